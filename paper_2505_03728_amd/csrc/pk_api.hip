@@ -468,6 +468,7 @@ int pk_robot_upload(pk_ctx *ctx, const pk_tree *t, int32_t *robot_id)
         R.chain_len = star ? L : 0;
     }
     build_path_layout(R);
+    build_fk_plan(R);
 
     RobotEntry ent;
     ent.host = R;
@@ -507,7 +508,7 @@ int pk_fk(pk_ctx *ctx, int32_t id, int64_t N, const float *q, float *ee_pose, fl
     if (!q || !ee_pose) return fail(ctx, PK_EINVAL, "pk_fk: NULL q or ee_pose");
     if (N > (int64_t)INT32_MAX * 32) return fail(ctx, PK_EUNSUPPORTED, "pk_fk: N too large");
     PK_HIP(ctx, hipSetDevice(ctx->device));
-    PK_HIP(ctx, launch_fk(r->dev, N, q, ee_pose, frames, (hipStream_t)stream));
+    PK_HIP(ctx, launch_fk(r->dev, r->host, N, q, ee_pose, frames, (hipStream_t)stream));
     return PK_OK;
 }
 

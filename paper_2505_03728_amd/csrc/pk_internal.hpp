@@ -44,6 +44,13 @@ constexpr int PK_LANE_MAX_CHAIN = 10; // longest single chain the per-lane kerne
 constexpr int PK_PATH_MAX_DEPTH = 16; // tree levels the path-pair wavefront kernel serves
 constexpr uint8_t PK_PATH_NONE = 0xff;
 
+// Forward-kinematics plan: where joint j's parent frame comes from (fk_from)
+// and where its own is kept (fk_save).
+constexpr int PK_FK_MAX_SLOTS = PK_MAX_JOINTS / 2;
+constexpr uint8_t PK_FK_RUN = 0xfe;    // fk_from: the frame just computed (joint j - 1)
+constexpr uint8_t PK_FK_BASE = 0xff;   // fk_from: the base
+constexpr uint8_t PK_FK_NONE = 0xff;   // fk_save: not kept
+
 // Path-pair layout of one problem on a 64-lane wavefront.  Lane l holds the
 // pair (joint[l], path group[l]): every joint on the path from the root to EE
 // k has a lane in group k, so a joint shared by several EE paths has one copy
@@ -95,6 +102,9 @@ struct RobotC {
     uint8_t step_of[PK_MAX_JOINTS];
     uint8_t step_pos[PK_MAX_JOINTS];
     PathC path;
+    int32_t fk_slots, pad3;                // saved frames live at once
+    uint8_t fk_from[PK_MAX_JOINTS], fk_save[PK_MAX_JOINTS];
+    uint8_t fk_ees[PK_MAX_JOINTS];         // bit k: EE k sits on this joint
 };
 
 // Uniform per-call data for the LM kernels (passed by value).
@@ -159,8 +169,8 @@ hipError_t launch_lm_path(const RobotC *dev_robot, const RobotC &host_robot,
                           const SolveParams &P, hipStream_t s, int persist_blocks = 0);
 hipError_t launch_best_of_k(const SolveParams &P, int n, int32_t *best_index,
                             float *best_joints, int32_t *success, hipStream_t s);
-hipError_t launch_fk(const RobotC *dev_robot, int64_t N, const float *q, float *ee_pose,
-                     float *joint_frames, hipStream_t s);
+hipError_t launch_fk(const RobotC *dev_robot, const RobotC &host_robot, int64_t N, const float *q,
+                     float *ee_pose, float *joint_frames, hipStream_t s);
 hipError_t launch_residual_jacobian(const RobotC *dev_robot, int64_t N, int32_t K,
                                     const float *targets, const float *q,
                                     const SolveParams &w, float *r, float *J, hipStream_t s);

@@ -740,7 +740,7 @@ int pk_seeder_train(pk_ctx *ctx, int32_t id, const float *q_train, int64_t S, in
         if (pose) (void)hipFree(pose);
         return fail(ctx, PK_ENOMEM, "pk_seeder_train: input buffers");
     }
-    hipError_t e = launch_fk(rb->dev, S, q_train, pose, nullptr, st);
+    hipError_t e = launch_fk(rb->dev, rb->host, S, q_train, pose, nullptr, st);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(sd::encode_kernel, dim3(sd::blocks(S, 256)), dim3(256), 0, st, S, S, pose, S,
                            1.f / s->reach, s->in_pad, (__bf16 *)nullptr, xall);

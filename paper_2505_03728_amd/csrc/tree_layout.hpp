@@ -41,6 +41,37 @@ inline void build_step_schedule(RobotC &R)
     R.nstep = ns;
 }
 
+// Forward-kinematics plan (R.fk_from, fk_save, fk_ees, fk_slots): joint j
+// continues from the frame of joint j - 1 when that is its parent, else from
+// a saved frame.  A frame is saved when some child is not the next joint, in
+// the lowest free slot, which is free again after the last such child.  A
+// live frame waits for a joint of its own, so at most PK_MAX_JOINTS / 2 are
+// live at once.  Needs R.n, R.m, the parents and the EEs' joints.
+inline void build_fk_plan(RobotC &R)
+{
+    int last[PK_MAX_JOINTS], slot_end[PK_FK_MAX_SLOTS];
+    for (int j = 0; j < R.n; ++j) {
+        last[j] = -1;
+        R.fk_ees[j] = 0;
+        const int par = R.j[j].parent;
+        if (par >= 0 && par != j - 1) last[par] = j;
+    }
+    for (int s = 0; s < PK_FK_MAX_SLOTS; ++s) slot_end[s] = -1;   // free
+    R.fk_slots = 0;
+    for (int j = 0; j < R.n; ++j) {
+        const int par = R.j[j].parent;
+        R.fk_from[j] = par < 0 ? PK_FK_BASE : par == j - 1 ? PK_FK_RUN : R.fk_save[par];
+        R.fk_save[j] = PK_FK_NONE;
+        if (last[j] < 0) continue;
+        int s = 0;   // joint j reads its parent's frame before it saves its own
+        while (slot_end[s] > j) ++s;
+        slot_end[s] = last[j];
+        R.fk_save[j] = (uint8_t)s;
+        if (s + 1 > R.fk_slots) R.fk_slots = s + 1;
+    }
+    for (int k = 0; k < R.m; ++k) R.fk_ees[R.e[k].joint] |= (uint8_t)(1u << k);
+}
+
 // Path-pair layout (PathC) of the wavefront kernel that gives each (joint,
 // EE path) pair a lane.  Leaves R.path.ok = 0 when the robot does not fit it
 // (mimic joints, more than PK_PATH_MAX_DEPTH levels, more than 64 pairs).
