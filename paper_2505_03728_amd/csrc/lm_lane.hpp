@@ -229,17 +229,32 @@ PK_DEV void eval_jacobian_chain(const RobotC *__restrict__ rb, const SolveParams
     }
 }
 
-// Limit and rest terms of joint i at q: its share of the normal matrix's
-// diagonal (dl^2 + w_rest^2) and of J^T r (dl rl + w_rest rr).
-PK_DEV void joint_terms(const RobotC *__restrict__ rb, const SolveParams &P, const float *__restrict__ qr,
-                        const float *q, int i, float &dg, float &gx)
+// Limit and rest terms of a joint at q (limits lo, hi, rest pose qr): its
+// share of the normal matrix's diagonal (dl^2 + w_rest^2) and of J^T r
+// (dl rl + w_rest rr).
+PK_DEV void joint_terms_at(const SolveParams &P, float q, float lo, float hi, float qr, float &dg, float &gx)
 {
-    const float over = q[i] - rb->j[i].hi, under = rb->j[i].lo - q[i];
+    const float over = q - hi, under = lo - q;
     const float rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
-    const float rr = P.w_rest * (q[i] - qr[i]);
+    const float rr = P.w_rest * (q - qr);
     const float dl = over > 0.f ? P.w_limit : (under > 0.f ? -P.w_limit : 0.f);
     dg = dl * dl + P.w_rest * P.w_rest;
     gx = dl * rl + P.w_rest * rr;
+}
+
+PK_DEV void joint_terms(const RobotC *__restrict__ rb, const SolveParams &P, const float *__restrict__ qr,
+                        const float *q, int i, float &dg, float &gx)
+{
+    joint_terms_at(P, q[i], rb->j[i].lo, rb->j[i].hi, qr[i], dg, gx);
+}
+
+// Squared limit and rest residuals of a joint.
+PK_DEV float joint_cost_at(const SolveParams &P, float q, float lo, float hi, float qr)
+{
+    const float over = q - hi, under = lo - q;
+    const float rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
+    const float rr = P.w_rest * (q - qr);
+    return rl * rl + rr * rr;
 }
 
 // Single chain: FP32 J^T J (+ diagonal terms) and J^T r at q straight from
@@ -297,12 +312,7 @@ PK_DEV bool eval_point1(const RobotC *__restrict__ rb, const SolveParams &P, con
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) cp += r[u] * r[u];
 #pragma unroll
-    for (int j = 0; j < L; ++j) {
-        const float over = q[j] - rb->j[j].hi, under = rb->j[j].lo - q[j];
-        const float rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
-        const float rr = P.w_rest * (q[j] - qr[j]);
-        cj += rl * rl + rr * rr;
-    }
+    for (int j = 0; j < L; ++j) cj += joint_cost_at(P, q[j], rb->j[j].lo, rb->j[j].hi, qr[j]);
     pcost = cp;
     cost = cp + cj;
     const bool take = first || cost < cur;

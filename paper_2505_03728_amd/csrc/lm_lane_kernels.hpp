@@ -7,7 +7,22 @@
 #include "lm_lane.hpp"
 
 namespace pk {
+
+// Four lanes per problem (lm_quad.hpp).
+namespace quad {
+template <int L, int KIND>
+hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const BestOut *best);
+}
+
 namespace lane {
+
+// Single-chain batches up to this size run with four lanes per problem: up
+// to here the quads of lanes give every SIMD at most one wavefront, which is
+// where the launch takes one wavefront's time whatever the batch.  30
+// iterations, four lanes against one: 90.6 against 131.1 us (7 joints), 64.5
+// against 89.1 (3), 127.8 against 224.2 (10) at 16384 problems; at 32768,
+// 130.7 against 137.5, 85.9 against 84.1 and 247.7 against 204.9.
+constexpr int64_t QUAD_MAX_PROBLEMS = 16384;
 
 // Next work item of this block: the block index for a plain grid, else an
 // atomic pop from the device queue (block = one wavefront).
@@ -112,6 +127,12 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
     const int block = BLOCK;
     int64_t grid = (P.N + block - 1) / block;
     const bool persist = P.queue_head != nullptr;
+    if constexpr (C == 1) {
+        if (!persist && !P.active && !P.n_active && !P.st_state && !P.target_exit && P.N <= QUAD_MAX_PROBLEMS) {
+            if (best && 64 % P.K != 0) return hipErrorInvalidValue;
+            return quad::launch<L, KIND>(rb, P, s, best);
+        }
+    }
     if (persist && persist_blocks > 0 && persist_blocks < grid) grid = persist_blocks;
     // rest pose: caller's array, else the robot's mid-range table
     const float *qr = P.q_rest ? P.q_rest : rb->mid;
@@ -141,3 +162,5 @@ hipError_t launch_lane_chain_c(int L, int kind, const RobotC *rb, const SolvePar
                                const BestOut *best);
 
 }  // namespace pk
+
+#include "lm_quad.hpp"

@@ -32,20 +32,26 @@ PK_DEV float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 PK_DEV float rsqrt_t(float d) { return __builtin_amdgcn_rsqf(d); }
 PK_DEV double rsqrt_t(double d) { return 1.0 / sqrt(d); }
 
+// One row of joint_step: the parent frame's row (o, pp) -> the row of
+// p = pp + Op t and O = Op G Rz(q) with (s, c) = (sin q, cos q).
+PK_DEV void joint_step_row(const float *o, float pp, const float *G, const float *t, float s, float c,
+                           float *On, float &pn)
+{
+    pn = pp + o[0] * t[0] + o[1] * t[1] + o[2] * t[2];
+    float m0 = o[0] * G[0] + o[1] * G[3] + o[2] * G[6];
+    float m1 = o[0] * G[1] + o[1] * G[4] + o[2] * G[7];
+    float m2 = o[0] * G[2] + o[1] * G[5] + o[2] * G[8];
+    On[0] = m0 * c + m1 * s;
+    On[1] = m1 * c - m0 * s;
+    On[2] = m2;
+}
+
 // p = pp + Op t;  O = Op G Rz(q) with (s, c) = (sin q, cos q).
 PK_DEV void joint_step(const float *Op, const float *pp, const float *G, const float *t,
                        float s, float c, float *O, float *p)
 {
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        p[r] = pp[r] + Op[3 * r] * t[0] + Op[3 * r + 1] * t[1] + Op[3 * r + 2] * t[2];
-        float m0 = Op[3 * r] * G[0] + Op[3 * r + 1] * G[3] + Op[3 * r + 2] * G[6];
-        float m1 = Op[3 * r] * G[1] + Op[3 * r + 1] * G[4] + Op[3 * r + 2] * G[7];
-        float m2 = Op[3 * r] * G[2] + Op[3 * r + 1] * G[5] + Op[3 * r + 2] * G[8];
-        O[3 * r] = m0 * c + m1 * s;
-        O[3 * r + 1] = m1 * c - m0 * s;
-        O[3 * r + 2] = m2;
-    }
+    for (int r = 0; r < 3; ++r) joint_step_row(Op + 3 * r, pp[r], G, t, s, c, O + 3 * r, p[r]);
 }
 
 // Prismatic joint: joint_step with s = 0, c = 1 leaves the frame unrotated;
@@ -57,17 +63,20 @@ PK_DEV void joint_slide(const float *O, float q, float *p)
     p[2] += q * O[8];
 }
 
+// One row of the EE frame R = O G, pe = p + O t.
+PK_DEV void ee_frame_row(const float *o, float p, const float *G, const float *t, float *R, float &pe)
+{
+    pe = p + o[0] * t[0] + o[1] * t[1] + o[2] * t[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) R[c] = o[0] * G[c] + o[1] * G[3 + c] + o[2] * G[6 + c];
+}
+
 // EE frame: R = O G, p = pe + O t.
 PK_DEV void ee_frame(const float *O, const float *p, const float *G, const float *t,
                      float *R, float *pe)
 {
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        pe[r] = p[r] + O[3 * r] * t[0] + O[3 * r + 1] * t[1] + O[3 * r + 2] * t[2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            R[3 * r + c] = O[3 * r] * G[c] + O[3 * r + 1] * G[3 + c] + O[3 * r + 2] * G[6 + c];
-    }
+    for (int r = 0; r < 3; ++r) ee_frame_row(O + 3 * r, p[r], G, t, R + 3 * r, pe[r]);
 }
 
 PK_DEV void mm3(const float *A, const float *B, float *C)
@@ -177,14 +186,10 @@ struct PoseLog {
     float sh, ch;      // sin(theta/2), cos(theta/2)
 };
 
-// Rt: target rotation; Re: EE rotation; d = p_ee - p_target (world frame).
-PK_DEV PoseLog pose_log(const float *Rt, const float *Re, const float *d)
+// log of the pose (RE, tE).
+PK_DEV PoseLog pose_log_of(const float *RE, const float *tE)
 {
     PoseLog L;
-    float RE[9], tE[3];
-    mTm3(Rt, Re, RE);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) tE[i] = Rt[i] * d[0] + Rt[3 + i] * d[1] + Rt[6 + i] * d[2];
     float w, x, y, z;
     rot_to_quat(RE, w, x, y, z);
     float s = sqrtf(x * x + y * y + z * z);
@@ -211,12 +216,36 @@ PK_DEV PoseLog pose_log(const float *Rt, const float *Re, const float *d)
     return L;
 }
 
-// Blocks of the right-Jacobian inverse folded with the EE rotation:
-//   J_r^-1(xi) = [[P, B], [0, P]],  P = J_l^-1(-phi),  B = -P Q(-rho,-phi) P,
-// M = P Re^T, N = B Re^T, so that for a joint with world axis w and point
-// velocity v (world), d xi / d q = [M v + N w ; M w].
-PK_DEV void jr_inv_blocks(const PoseLog &L, const float *Re, float *M, float *N)
+// Rt: target rotation; Re: EE rotation; d = p_ee - p_target (world frame).
+PK_DEV PoseLog pose_log(const float *Rt, const float *Re, const float *d)
 {
+    float RE[9], tE[3];
+    mTm3(Rt, Re, RE);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) tE[i] = Rt[i] * d[0] + Rt[3 + i] * d[1] + Rt[6 + i] * d[2];
+    return pose_log_of(RE, tE);
+}
+
+// Scalars and vectors of the right-Jacobian-inverse blocks (jr_inv_blocks).
+struct JrCoef {
+    float k, a1, a2;
+    float pd, qd, qf;   // diagonals of P and Q, coefficient of f f^T in Q
+    float c[3], sk[3];  // f x r, skew part of Q
+};
+
+// With f = phi, r = rho, d = f.r, c = f x r, t2 = |f|^2 and the identity
+// hat(a) hat(b) = b a^T - (a.b) I, the products of hats in P and Q reduce
+// to outer products:
+//   Ph Ph = f f^T - t2 I,
+//   Ph Rh + Rh Ph - Ph Rh Ph = r f^T + f r^T - 2 d I + d Ph,
+//   3 Ph Rh Ph - Ph Ph Rh - Rh Ph Ph = f c^T - c f^T - d Ph,
+//   Ph Rh Ph Ph + Ph Ph Rh Ph = -2 d (f f^T - t2 I),
+// so P = I + Ph/2 + k (f f^T - t2 I) and
+//   Q(-rho,-phi) = hat((a1 - a2) d f - r/2) + a1 (r f^T + f r^T)
+//                + a2 (f c^T - c f^T) - 2 a3 d f f^T + 2 d (a3 t2 - a1) I.
+PK_DEV JrCoef jr_coef(const PoseLog &L)
+{
+    JrCoef J;
     const float th = L.theta, t2 = th * th;
     float k, a1, a2, a3;
     if (th < 0.1f)
@@ -234,37 +263,44 @@ PK_DEV void jr_inv_blocks(const PoseLog &L, const float *Re, float *M, float *N)
         a2 = (t2 - 4.f * L.sh * L.sh) * (0.5f * it2 * it2);   // 2 cos - 2 = -4 sin^2(th/2)
         a3 = (2.f * th - 3.f * st + th * ct) * (0.5f * it3 * it2);
     }
-    // With f = phi, r = rho, d = f.r, c = f x r, t2 = |f|^2 and the identity
-    // hat(a) hat(b) = b a^T - (a.b) I, the products of hats in P and Q reduce
-    // to outer products:
-    //   Ph Ph = f f^T - t2 I,
-    //   Ph Rh + Rh Ph - Ph Rh Ph = r f^T + f r^T - 2 d I + d Ph,
-    //   3 Ph Rh Ph - Ph Ph Rh - Rh Ph Ph = f c^T - c f^T - d Ph,
-    //   Ph Rh Ph Ph + Ph Ph Rh Ph = -2 d (f f^T - t2 I),
-    // so P = I + Ph/2 + k (f f^T - t2 I) and
-    //   Q(-rho,-phi) = hat((a1 - a2) d f - r/2) + a1 (r f^T + f r^T)
-    //                + a2 (f c^T - c f^T) - 2 a3 d f f^T + 2 d (a3 t2 - a1) I.
     const float *f = L.phi, *r = L.rho;
     const float d = f[0] * r[0] + f[1] * r[1] + f[2] * r[2];
     const float ff2 = f[0] * f[0] + f[1] * f[1] + f[2] * f[2];   // t2 of the identities
-    float c[3];
-    cross(f, r, c);
-    float P[9], Q[9];
-    const float pd = 1.f - k * ff2;                       // diagonal of P
-    const float qd = 2.f * d * (a3 * ff2 - a1);           // diagonal of Q
-    const float qf = -2.f * a3 * d;                       // f f^T coefficient of Q
-    float sk[3];                                          // skew part of Q
+    cross(f, r, J.c);
+    J.pd = 1.f - k * ff2;
+    J.qd = 2.f * d * (a3 * ff2 - a1);
+    J.qf = -2.f * a3 * d;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) sk[i] = (a1 - a2) * d * f[i] - 0.5f * r[i];
+    for (int i = 0; i < 3; ++i) J.sk[i] = (a1 - a2) * d * f[i] - 0.5f * r[i];
+    J.k = k;
+    J.a1 = a1;
+    J.a2 = a2;
+    return J;
+}
+
+// Entries (i, j) of P and Q without their hat parts; fi, ri, ci: component i
+// of f, r and c.
+PK_DEV void jr_entry(const JrCoef &J, const float *f, const float *r, float fi, float ri, float ci, int j,
+                     bool diag, float &p, float &q)
+{
+    const float ff = fi * f[j];
+    p = J.k * ff + (diag ? J.pd : 0.f);
+    q = J.a1 * (ri * f[j] + fi * r[j]) + J.a2 * (fi * J.c[j] - ci * f[j]) + J.qf * ff + (diag ? J.qd : 0.f);
+}
+
+// Blocks of the right-Jacobian inverse folded with the EE rotation:
+//   J_r^-1(xi) = [[P, B], [0, P]],  P = J_l^-1(-phi),  B = -P Q(-rho,-phi) P,
+// M = P Re^T, N = B Re^T, so that for a joint with world axis w and point
+// velocity v (world), d xi / d q = [M v + N w ; M w].
+PK_DEV void jr_inv_blocks(const PoseLog &L, const float *Re, float *M, float *N)
+{
+    const JrCoef J = jr_coef(L);
+    const float *f = L.phi, *r = L.rho, *sk = J.sk;
+    float P[9], Q[9];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const float ff = f[i] * f[j];
-            P[3 * i + j] = k * ff + (i == j ? pd : 0.f);
-            Q[3 * i + j] = a1 * (r[i] * f[j] + f[i] * r[j]) + a2 * (f[i] * c[j] - c[i] * f[j]) + qf * ff +
-                           (i == j ? qd : 0.f);
-        }
+        for (int j = 0; j < 3; ++j) jr_entry(J, f, r, f[i], r[i], J.c[i], j, i == j, P[3 * i + j], Q[3 * i + j]);
     // + hat(f)/2 on P, + hat(sk) on Q
     P[1] -= 0.5f * f[2]; P[2] += 0.5f * f[1]; P[5] -= 0.5f * f[0];
     P[3] += 0.5f * f[2]; P[6] -= 0.5f * f[1]; P[7] += 0.5f * f[0];
