@@ -11,6 +11,11 @@ bool lane_variant_available(int chains, int chain_len, int kind)
            (chains == 4 && chain_len == 4 && kind == PK_EE_POSITION);
 }
 
+bool lane_takes_best(const RobotC &h, const SolveParams &P)
+{
+    return 64 % P.K == 0 || (lane::takes_quad(h.chains, h.chain_len, P) && P.K <= 64);
+}
+
 hipError_t launch_lm_lane(const RobotC *dev_robot, const RobotC &h, const SolveParams &P,
                           hipStream_t s, int persist_blocks, const BestOut *best)
 {

@@ -16,13 +16,22 @@ hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const B
 
 namespace lane {
 
-// Single-chain batches up to this size run with four lanes per problem: up
-// to here the quads of lanes give every SIMD at most one wavefront, which is
-// where the launch takes one wavefront's time whatever the batch.  30
-// iterations, four lanes against one: 90.6 against 131.1 us (7 joints), 64.5
-// against 89.1 (3), 127.8 against 224.2 (10) at 16384 problems; at 32768,
-// 130.7 against 137.5, 85.9 against 84.1 and 247.7 against 204.9.
-constexpr int64_t QUAD_MAX_PROBLEMS = 16384;
+// Single-chain batches up to this size run with four lanes per problem: at
+// 16384 problems the quads give every SIMD one wavefront; chains of up to 8
+// joints fit two per SIMD (longer ones need more than 256 registers), which
+// takes less than twice as long as one, and the per-lane kernel's time hardly
+// depends on the batch up to 65536.  30 iterations with early exit, four
+// lanes against one, us: 7 joints 87.5 / 131.1 at 16384, 124.1 / 137.5 at
+// 32768, 181.5 / 135.8 at 49152; 3 joints 61.7 / 89.1, 82.6 / 83.7, 109.5 /
+// 83.5; 10 joints 118.3 / 224.2, 228.0 / 204.3; without the rest term (the
+// redundant chains' steps then end in the FP64 re-solve) 7 joints 113.3 /
+// 219.1, 142.9 / 216.4, 213.8 / 232.1.
+inline int64_t quad_max_problems(int chain_len) { return chain_len <= 8 ? 32768 : 16384; }
+// (target_exit is defined on the per-lane kernel's runs of lanes.)
+inline bool takes_quad(int chains, int chain_len, const SolveParams &P)
+{
+    return chains == 1 && !P.target_exit && P.N <= quad_max_problems(chain_len);
+}
 
 // Next work item of this block: the block index for a plain grid, else an
 // atomic pop from the device queue (block = one wavefront).
@@ -128,10 +137,8 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
     int64_t grid = (P.N + block - 1) / block;
     const bool persist = P.queue_head != nullptr;
     if constexpr (C == 1) {
-        if (!persist && !P.active && !P.n_active && !P.st_state && !P.target_exit && P.N <= QUAD_MAX_PROBLEMS) {
-            if (best && 64 % P.K != 0) return hipErrorInvalidValue;
+        if (!persist && !P.active && !P.n_active && !P.st_state && takes_quad(C, L, P))
             return quad::launch<L, KIND>(rb, P, s, best);
-        }
     }
     if (persist && persist_blocks > 0 && persist_blocks < grid) grid = persist_blocks;
     // rest pose: caller's array, else the robot's mid-range table

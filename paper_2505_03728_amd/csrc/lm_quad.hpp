@@ -22,10 +22,12 @@
 // bit for bit.  Control flow is uniform over a quad: a lane that reads
 // another by quad_perm finds it active.
 //
-// Bound: one wavefront's instruction stream (about 1.1 k VALU instructions
-// per iteration for 7 joints, and the latencies that one wavefront per SIMD
-// does not hide).  8 problems x 30 iterations, 7 joints: 148.0 -> 95.5 us;
-// 16384 problems of the mobile base (10 joints): 223.5 -> 126.3 us.
+// Bound: one wavefront's instruction stream (about 1.3 k instructions per
+// iteration for 7 joints, and the latencies that one wavefront per SIMD does
+// not hide).  Against one lane per problem, 30 iterations: 8 problems of 7
+// joints 145.8 -> 91.5 us; 16384 of the mobile base (10 joints) 226.3 ->
+// 115.4; 16384 of 7 joints without the rest term, where most steps end in the
+// FP64 re-solve, 219.1 -> 113.3 (183.0 with the per-lane kernel's re-solve).
 #pragma once
 
 #include "lm_lane_kernels.hpp"
@@ -49,8 +51,18 @@ PK_DEV float from(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(i, S * 0x55, 0xf, 0xf, true));
 }
 
+template <int S>
+PK_DEV double from(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, S * 0x55, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), S * 0x55, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // The same with the lane as a value known after unrolling.
-PK_DEV float from(float v, int s)
+template <typename T>
+PK_DEV T from(T v, int s)
 {
     return s == 0 ? from<0>(v) : s == 1 ? from<1>(v) : s == 2 ? from<2>(v) : from<3>(v);
 }
@@ -100,41 +112,79 @@ struct Lane {
     float lo[Geo<L, KIND>::NS], hi[Geo<L, KIND>::NS], qr[Geo<L, KIND>::NS];
     bool pris[Geo<L, KIND>::NS];
     float tp, Rt[3];                        // target position's component, column `row` of its rotation
+    // Joint and EE transforms (G, then t).  Read with scalar loads where they
+    // are used, each joint's wait for them stood in the one wavefront's way.
+    float fr[L + 1][12];
     float *ex;                              // the problem's exchange area
 };
 
 // a[min(r, n - 1)] of the N values a (n at most 4), by selects.  The values
 // are opaque to the optimiser, which otherwise turns the selects into one
 // load at a lane-dependent address and keeps the array in scratch memory.
-template <int N>
-PK_DEV float pick(int r, const float *a)
+template <int N, typename T>
+PK_DEV T pick(int r, const T *a)
 {
-    float v = a[0];
+    T v = a[0];
     asm("" : "+v"(v));
 #pragma unroll
     for (int i = 1; i < N; ++i) {
-        float w = a[i];
+        T w = a[i];
         asm("" : "+v"(w));
         v = r >= i ? w : v;
     }
     return v;
 }
 
-// Normal equations of the taken point on this lane: rows 4 s + r of J^T J
-// (entries up to the diagonal), the diagonal entry with its limit and rest
-// terms, and J^T r.
+// The taken point on this lane: Jacobian columns of the own joints, their
+// limit and rest terms (of the diagonal, of J^T r) and the residual rows.
 template <int L, int KIND>
-struct Normal {
-    float A[Geo<L, KIND>::NS][L];
-    float dg[Geo<L, KIND>::NS], g[Geo<L, KIND>::NS];
+struct Point {
+    float col[Geo<L, KIND>::NS][Geo<L, KIND>::ROWS], dq[Geo<L, KIND>::NS], gx[Geo<L, KIND>::NS];
+    float r[Geo<L, KIND>::ROWS];
 };
 
+// Its normal equations in precision T: rows 4 s + r of J^T J (entries up to
+// the diagonal), the diagonal entry with its limit and rest terms, and J^T r.
+template <int L, typename T>
+struct Normal {
+    static constexpr int NS = (L + 3) / 4;
+    T A[NS][L], dg[NS], g[NS];
+};
+
+template <int L, int KIND, typename T>
+PK_DEV void form_normal(int lr, const Point<L, KIND> &X, Normal<L, T> &E)
+{
+    constexpr int NS = Geo<L, KIND>::NS, ROWS = Geo<L, KIND>::ROWS;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+#pragma unroll
+        for (int k = 0; k < L; ++k) E.A[s][k] = 0;
+    }
+#pragma unroll
+    for (int k = 0; k < L; ++k)
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const T ck = (T)from(X.col[k / 4][u], k % 4);
+#pragma unroll
+            for (int s = k / 4; s < NS; ++s) E.A[s][k] += (T)X.col[s][u] * ck;
+        }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        E.dg[s] = (L - 4 * s >= 4 ? pick<4>(lr, E.A[s] + 4 * s) : pick<(L % 4 ? L % 4 : 4)>(lr, E.A[s] + 4 * s)) +
+                  (T)X.dq[s];
+        T b = (T)X.gx[s];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) b += (T)X.col[s][u] * (T)X.r[u];
+        E.g[s] = b;
+    }
+}
+
 // One point: cost and errors at q and, when it is taken (lane::eval_point1's
-// rule), its normal equations.
+// rule), what its normal equations are formed from.  Whether it was taken.
 template <int L, int KIND>
-PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, const Lane<L, KIND> &Q,
+PK_DEV bool eval_point(const RobotC *__restrict__ rb, const SolveParams &P, const Lane<L, KIND> &Q,
                        const float *q, bool first, float cur, float &cost, float &pcost, float &perr,
-                       float &rerr, Normal<L, KIND> &E)
+                       float &rerr, Point<L, KIND> &X)
 {
     using G = Geo<L, KIND>;
     constexpr int NS = G::NS, ROWS = G::ROWS;
@@ -156,7 +206,7 @@ PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
 #pragma unroll
     for (int j = 0; j < L; ++j) {
         float on[3], pn;
-        joint_step_row(o, p, rb->j[j].G, rb->j[j].t, from(so[j / 4], j % 4), from(co[j / 4], j % 4), on, pn);
+        joint_step_row(o, p, Q.fr[j], Q.fr[j] + 9, from(so[j / 4], j % 4), from(co[j / 4], j % 4), on, pn);
         if (pris_of(KIND) && rb->j[j].type == PK_JOINT_PRISMATIC) pn += q[j] * on[2];   // joint_slide
 #pragma unroll
         for (int u = 0; u < 3; ++u) o[u] = on[u];
@@ -165,7 +215,7 @@ PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
         Q.ex[j * G::JW + 3 + Q.row] = p;
     }
     float Re[3], pe;
-    ee_frame_row(o, p, rb->e[0].G, rb->e[0].t, Re, pe);
+    ee_frame_row(o, p, Q.fr[L], Q.fr[L] + 9, Re, pe);
     // residual rows
     const float dr = pe - Q.tp;
     const float d[3] = {from<0>(dr), from<1>(dr), from<2>(dr)};
@@ -205,7 +255,7 @@ PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
     for (int j = 0; j < L; ++j) cj += from(jc[j / 4], j % 4);
     pcost = cp;
     cost = cp + cj;
-    if (!(first || cost < cur)) return;
+    if (!(first || cost < cur)) return false;
 
     // own Jacobian columns: lane::jac_column on the own joints' axes and
     // origins, M and N of jr_inv_blocks by rows, then whole on every lane
@@ -246,7 +296,6 @@ PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
             }
     }
     exchange();
-    float col[NS][ROWS], gx[NS], dq[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int j = min(4 * s + Q.r, L - 1);
@@ -256,45 +305,27 @@ PK_DEV void eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
             om[u] = Q.ex[j * G::JW + u];
             pj[u] = Q.ex[j * G::JW + 3 + u];
         }
-        lane::jac_column<KIND>(P, M, N, om, pj, pev, pris_of(KIND) && Q.pris[s], col[s]);
-        lane::joint_terms_at(P, qo[s], Q.lo[s], Q.hi[s], Q.qr[s], dq[s], gx[s]);
+        lane::jac_column<KIND>(P, M, N, om, pj, pev, pris_of(KIND) && Q.pris[s], X.col[s]);
+        lane::joint_terms_at(P, qo[s], Q.lo[s], Q.hi[s], Q.qr[s], X.dq[s], X.gx[s]);
     }
     exchange();   // the next point's frames overwrite the area
-    // own rows of J^T J and J^T r
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-            if (k > 4 * s + 3) continue;
-            float a = 0.f;
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) a += col[s][u] * from(col[k / 4][u], k % 4);
-            E.A[s][k] = a;
-        }
-        E.dg[s] = (L - 4 * s >= 4 ? pick<4>(Q.r, E.A[s] + 4 * s) : pick<(L % 4 ? L % 4 : 4)>(Q.r, E.A[s] + 4 * s)) +
-                  dq[s];
-        float b = gx[s];
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u) b += col[s][u] * r[u];
-        E.g[s] = b;
-    }
+    for (int u = 0; u < ROWS; ++u) X.r[u] = r[u];
+    return true;
 }
 
-// Damped step: lane::lane_step's test and values, the factor right-looking
-// with rows over the quad.  x whole on every lane; false on a small pivot.
-template <int L, int KIND>
-PK_DEV bool step(const SolveParams &P, int r, const Normal<L, KIND> &E, float lam, float *x)
+// x = -(A + lam diag(max(A_ii, floor)))^-1 g, whole on every lane: the values
+// of lane::chol_damped and chol_solve_neg, the factor right-looking with its
+// rows over the quad.  False if a pivot is not above thresh (or not finite).
+template <int L, typename T>
+PK_DEV bool solve(int r, const Normal<L, T> &E, T lam, T floor_, T thresh, T *x)
 {
-    constexpr int NS = Geo<L, KIND>::NS;
-    float dmax = 0.f, F[NS][L], ys[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) dmax = fmaxf(dmax, E.dg[s] + lam * fmaxf(E.dg[s], P.damping_floor));
-    dmax = quad_max(dmax);
-    const float thresh = P.pivot_rel * dmax;
+    constexpr int NS = Normal<L, T>::NS;
+    T F[NS][L], ys[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        float dd = E.dg[s];
-        dd += lam * (E.dg[s] > P.damping_floor ? E.dg[s] : P.damping_floor);
+        T dd = E.dg[s];
+        dd += lam * (E.dg[s] > floor_ ? E.dg[s] : floor_);
 #pragma unroll
         for (int k = 0; k < L; ++k) {
             if (k > 4 * s + 3) continue;
@@ -303,13 +334,13 @@ PK_DEV bool step(const SolveParams &P, int r, const Normal<L, KIND> &E, float la
         ys[s] = -E.g[s];
     }
     bool ok = true;
-    float inv[L], y[L];
+    T inv[L], y[L];
 #pragma unroll
     for (int l = 0; l < L; ++l) {
-        float d = from(F[l / 4][l], l % 4);
-        if (!(d > thresh) || !(d < INFINITY)) {
+        T d = from(F[l / 4][l], l % 4);
+        if (!(d > thresh) || !(d < (T)INFINITY)) {
             ok = false;
-            d = 1.f;
+            d = 1;
         }
         inv[l] = rsqrt_t(d);
         y[l] = from(ys[l / 4], l % 4) * inv[l];
@@ -321,7 +352,7 @@ PK_DEV bool step(const SolveParams &P, int r, const Normal<L, KIND> &E, float la
         }
 #pragma unroll
         for (int k = l + 1; k < L; ++k) {
-            const float lk = from(F[k / 4][l], k % 4);
+            const T lk = from(F[k / 4][l], k % 4);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 if (k > 4 * s + 3) continue;
@@ -331,11 +362,35 @@ PK_DEV bool step(const SolveParams &P, int r, const Normal<L, KIND> &E, float la
     }
 #pragma unroll
     for (int i = L - 1; i >= 0; --i) {
-        float t = y[i];
+        T t = y[i];
 #pragma unroll
         for (int l = i + 1; l < L; ++l) t -= from(F[l / 4][i], l % 4) * x[l];
         x[i] = t * inv[i];
     }
+    return ok;
+}
+
+// Damped step from the taken point: lane::lane_step's pivot test on the
+// FP32 factor and the FP64 re-solve, here from the columns the point kept
+// (the per-lane kernel, short of registers, forms them again).  False if
+// that fails too.
+template <int L, int KIND>
+PK_DEV bool step(const SolveParams &P, int r, const Point<L, KIND> &X, const Normal<L, float> &E, float lam,
+                 int &flags, float *delta)
+{
+    constexpr int NS = Geo<L, KIND>::NS;
+    float dmax = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) dmax = fmaxf(dmax, E.dg[s] + lam * fmaxf(E.dg[s], P.damping_floor));
+    dmax = quad_max(dmax);
+    if (solve<L, float>(r, E, lam, P.damping_floor, P.pivot_rel * dmax, delta)) return true;
+    flags |= PK_FLAG_FP64;
+    Normal<L, double> D;
+    double x[L];
+    form_normal<L, KIND, double>(r, X, D);
+    const bool ok = solve<L, double>(r, D, (double)lam, (double)P.damping_floor, 0.0, x);
+#pragma unroll
+    for (int j = 0; j < L; ++j) delta[j] = (float)x[j];
     return ok;
 }
 
@@ -369,6 +424,14 @@ PK_DEV void quad_problem(const RobotC *__restrict__ rb, const float *__restrict_
         Q.qr[s] = qr[j];
         Q.pris[s] = pris_of(KIND) && rb->j[j].type == PK_JOINT_PRISMATIC;
     }
+#pragma unroll
+    for (int j = 0; j <= L; ++j)
+#pragma unroll
+        for (int u = 0; u < 12; ++u) {
+            Q.fr[j][u] = j < L ? (u < 9 ? rb->j[j].G[u] : rb->j[j].t[u - 9])
+                               : (u < 9 ? rb->e[0].G[u] : rb->e[0].t[u - 9]);
+            asm("" : "+v"(Q.fr[j][u]));     // in vector registers over the whole solve
+        }
     exchange();
     Q.tp = S[Q.row];
     if constexpr (ee_of(KIND) == PK_EE_POSE) {
@@ -378,23 +441,21 @@ PK_DEV void quad_problem(const RobotC *__restrict__ rb, const float *__restrict_
     int iters = 0, accepts = 0, itt = -1, flags = 0;
     bool done = false, stalled = false, first = true;
     float lam = P.lambda0, cost = 0.f, pcost = 0.f, perr[1] = {0.f}, rerr[1] = {0.f};
-    Normal<L, KIND> E;
+    Point<L, KIND> X;
+    Normal<L, float> E;
 #pragma unroll
     for (int j = 0; j < L; ++j) qt[j] = q[j];
     for (;;) {
         bool ok = true;
         if (!first) {
             float delta[L];
-            ok = step<L, KIND>(P, Q.r, E, lam, delta);
-            if (!ok) {
-                flags |= PK_FLAG_FP64;
-                ok = lane::step_fp64_1<L, KIND>(rb, P, qr, S, q, lam, delta);
-            }
+            ok = step<L, KIND>(P, Q.r, X, E, lam, flags, delta);
 #pragma unroll
             for (int j = 0; j < L; ++j) qt[j] = q[j] + delta[j];
         }
         float ct = INFINITY, pct = 0.f, pe_t[1] = {0.f}, re_t[1] = {0.f};
-        if (ok) eval_point<L, KIND>(rb, P, Q, qt, first, cost, ct, pct, pe_t[0], re_t[0], E);
+        if (ok && eval_point<L, KIND>(rb, P, Q, qt, first, cost, ct, pct, pe_t[0], re_t[0], X))
+            form_normal<L, KIND, float>(Q.r, X, E);
         if (first) {
             cost = ct;
             pcost = pct;
@@ -439,30 +500,31 @@ PK_DEV void quad_problem(const RobotC *__restrict__ rb, const float *__restrict_
     fin->conv = lane::meets_tol<1, L, KIND>(P, perr, rerr);
 }
 
-// 64 problems per workgroup of four wavefronts; with B's pointers set, their
-// targets' best-of-K as well (K divides 64).
+// Up to 64 problems per workgroup of four wavefronts; with B's pointers set,
+// whole targets per workgroup (K at most 64) and their best-of-K as well.
 template <int L, int KIND>
 __global__ __launch_bounds__(THREADS) void lm_quad_kernel(const RobotC *__restrict__ rb,
                                                           const float *__restrict__ qr, SolveParams P,
-                                                          BestOut B)
+                                                          BestOut B, int per_block)
 {
     using G = Geo<L, KIND>;
     __shared__ __attribute__((aligned(16))) float smem[G::FLOATS];
     __shared__ float bc[PROBLEMS], bp[PROBLEMS];
     __shared__ int bv[PROBLEMS];
-    const int64_t base = (int64_t)blockIdx.x * PROBLEMS, p = base + (threadIdx.x >> 2);
-    const bool live = p < P.N;
+    const int slot = threadIdx.x >> 2;
+    const int64_t p = (int64_t)blockIdx.x * per_block + slot;
+    const bool live = slot < per_block && p < P.N;
     LaneFinal<L> fin;
     if (live) quad_problem<L, KIND>(rb, qr, P, smem, p, &fin);
     if (!(B.index || B.joints || B.success)) return;   // uniform
     if (live && (threadIdx.x & 3) == 0) {
-        bc[threadIdx.x >> 2] = fin.cost;
-        bp[threadIdx.x >> 2] = fin.pcost;
-        bv[threadIdx.x >> 2] = fin.conv ? PK_CONVERGED : PK_MAX_ITERS;
+        bc[slot] = fin.cost;
+        bp[slot] = fin.pcost;
+        bv[slot] = fin.conv ? PK_CONVERGED : PK_MAX_ITERS;
     }
     __syncthreads();
     if (!live) return;
-    const int K = P.K, slot = threadIdx.x >> 2, first = slot / K * K;
+    const int K = P.K, first = slot / K * K;
     bool any;
     const int b = best_of_k_pick(bv, bc, bp, first, K, any);
     if (slot != first + b || (threadIdx.x & 3)) return;
@@ -478,9 +540,11 @@ template <int L, int KIND>
 hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const BestOut *best)
 {
     const float *qr = P.q_rest ? P.q_rest : rb->mid;
+    if (best && P.K > PROBLEMS) return hipErrorInvalidValue;
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
-    hipLaunchKernelGGL((lm_quad_kernel<L, KIND>), dim3((unsigned)((P.N + PROBLEMS - 1) / PROBLEMS)), dim3(THREADS),
-                       0, s, rb, qr, P, B);
+    const int per_block = best ? PROBLEMS / P.K * P.K : PROBLEMS;
+    const dim3 grid((unsigned)((P.N + per_block - 1) / per_block));
+    hipLaunchKernelGGL((lm_quad_kernel<L, KIND>), grid, dim3(THREADS), 0, s, rb, qr, P, B, per_block);
     return hipGetLastError();
 }
 

@@ -569,10 +569,10 @@ static int ik_solve_impl(pk_ctx *ctx, int32_t id, const pk_ik_problem *pr, const
 
     PK_HIP(ctx, hipSetDevice(ctx->device));
     const bool want_best = out->best_index || out->best_joints || out->target_success;
-    // The per-lane kernel takes best-of-K itself when a target's K problems
-    // share a wavefront (K divides 64): one launch instead of two, and the
-    // costs and statuses need not go through memory.
-    const bool fuse = want_best && variant == PK_VARIANT_LANE && 64 % pr->K == 0;
+    // Best-of-K in the LM launch where it can: one launch instead of two, and
+    // the costs and statuses need not go through memory.
+    P.K = pr->K; P.N = N; P.T = pr->n_targets;
+    const bool fuse = want_best && variant == PK_VARIANT_LANE && lane_takes_best(H, P);
     // Workspace: pose-only cost, total cost and status when a separate
     // best-of-K pass needs them and the caller did not ask for them.
     float *ws_f = nullptr;
@@ -587,7 +587,6 @@ static int ik_solve_impl(pk_ctx *ctx, int32_t id, const pk_ik_problem *pr, const
         }
     }
 
-    P.K = pr->K; P.N = N; P.T = pr->n_targets;
     P.targets = pr->targets; P.seeds = pr->seeds;
     P.joints = out->joints; P.pos_err = out->pos_err; P.rot_err = out->rot_err;
     P.pose_cost = out->pose_cost ? out->pose_cost : (ws_f ? ws_f : nullptr);

@@ -144,8 +144,8 @@ struct SolveParams {
 #define PK_ST_DONE 0x10000
 #define PK_ST_STALLED 0x20000
 
-// Best-of-K outputs written by the per-lane kernel itself (its K problems of
-// a target share a wavefront when K divides 64); NULL pointers are skipped.
+// Best-of-K outputs written by the LM launch itself (lane_takes_best); NULL
+// pointers are skipped.
 struct BestOut {
     int32_t *index;
     float *joints;     // [n][T]
@@ -155,9 +155,13 @@ struct BestOut {
 // Launchers (defined next to their kernels).  Return hipSuccess or the
 // launch error.
 bool lane_variant_available(int chains, int chain_len, int kind);
+// Whether a plain launch (no queue, no active list) can take best-of-K
+// itself: K divides 64, so that a target's problems share a wavefront, or the
+// batch runs with four lanes per problem and K is at most 64, so that they
+// share a workgroup.  Reads P.K, P.N and P.target_exit.
+bool lane_takes_best(const RobotC &host_robot, const SolveParams &P);
 // persist_blocks: grid size when P.queue_head is set (0 = one block per item).
-// best (non-persistent launches without an active list, K dividing 64 only):
-// best-of-K in the same launch.
+// best (where lane_takes_best): best-of-K in the same launch.
 hipError_t launch_lm_lane(const RobotC *dev_robot, const RobotC &host_robot,
                           const SolveParams &P, hipStream_t s, int persist_blocks = 0,
                           const BestOut *best = nullptr);
