@@ -19,6 +19,7 @@
 
 #include "sd_gemm.hpp"
 #include "sd_mlp.hpp"
+#include "sd_train.hpp"
 
 namespace pk {
 namespace sd {
@@ -276,6 +277,7 @@ struct SeederState {
     // BF16 weights in MFMA fragment order for the fused inference pass,
     // rebuilt from Pb after the parameters change.
     __bf16 *Wf = nullptr;
+    __bf16 *Wt = nullptr;               // the same of the transposed weights (training)
     std::vector<int64_t> wfoff;
     bool wf_dirty = true;
     std::vector<void *> extra;
@@ -285,7 +287,7 @@ void seeder_free(SeederState *s)
 {
     if (!s) return;
     void *ptrs[] = {s->P, s->G, s->M, s->V, s->Pb, s->dstep, s->X0, s->Hb, s->dZb, s->dYb, s->Z,
-                    s->Y, s->dZ, s->dY, s->Q, s->part, s->splitbuf, s->Wf};
+                    s->Y, s->dZ, s->dY, s->Q, s->part, s->splitbuf, s->Wf, s->Wt};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (void *p : s->extra)
@@ -306,15 +308,15 @@ int alloc_acts(pk_ctx *ctx, SeederState *s, int64_t rows)
     bool ok = true;
     ok &= hipMalloc(&s->X0, rows * s->in_pad * sizeof(__bf16)) == hipSuccess;
     ok &= hipMalloc(&s->Hb, (size_t)L * hsz * sizeof(__bf16)) == hipSuccess;
-    ok &= hipMalloc(&s->dZb, hsz * sizeof(__bf16)) == hipSuccess;
+    ok &= hipMalloc(&s->dZb, (size_t)L * hsz * sizeof(__bf16)) == hipSuccess;
     ok &= hipMalloc(&s->dYb, rows * s->out_pad * sizeof(__bf16)) == hipSuccess;
     ok &= hipMalloc(&s->Z, (size_t)L * hsz * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->Y, rows * s->out_pad * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->dZ, hsz * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->dY, rows * s->out_pad * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->Q, rows * s->n * sizeof(float)) == hipSuccess;
-    // column-sum partials (one row per 128-row chunk) or loss partials (one per 16 rows)
-    ok &= hipMalloc(&s->part, ((rows / sd::COLSUM_ROWS + 1) * (size_t)std::max(s->H, s->out_pad) +
+    // column-sum partials (one row per 128-row chunk) of every layer, loss partials (one per 16 rows)
+    ok &= hipMalloc(&s->part, ((rows / sd::COLSUM_ROWS + 1) * (size_t)(L * s->H + s->out_pad) +
                                rows / 16 + 1) * sizeof(float) + 4096) == hipSuccess;
     // Split-K partials: sized for the largest split any row count can pick.
     size_t need = 0;
@@ -536,7 +538,7 @@ int pk_seeder_create(pk_ctx *ctx, int32_t robot_id, int32_t K, int32_t hidden, i
         s->wfoff.push_back(wfn);
         wfn += (int64_t)s->lin[l] * s->lout[l];
     }
-    ok = ok && hipMalloc(&s->Wf, wfn * 2) == hipSuccess;
+    ok = ok && hipMalloc(&s->Wf, wfn * 2) == hipSuccess && hipMalloc(&s->Wt, wfn * 2) == hipSuccess;
     if (!ok) {
         seeder_free(s);
         return fail(ctx, PK_ENOMEM, "pk_seeder_create: allocation failed");
@@ -630,6 +632,112 @@ hipError_t loss_and_grads(SeederState *s, int64_t rows, int64_t B, float *loss_l
     return backward(s, rows, st);
 }
 
+// The three-launch training step (sd_train.hpp) serves up to 3 hidden layers
+// of width 128, 256 or 512; other shapes train layer by layer.
+bool train_fused(const SeederState *s)
+{
+    return s->in_pad == 32 && s->out_pad == 64 && (s->H == 128 || s->H == 256 || s->H == 512) &&
+           s->depth < sd::TR_MAX_LAYERS;
+}
+
+struct TrainPlan {
+    sd::TrainNet net;
+    sd::TrainActs acts;
+    sd::DwPlan dw;
+    sd::FinishPlan fin;
+    int dw_wgs, fin_wgs;
+};
+
+TrainPlan train_plan(SeederState *s, int64_t rows)
+{
+    using namespace sd;
+    TrainPlan t{};
+    const int L = s->depth;
+    const size_t hsz = (size_t)rows * s->H;
+    t.net.depth = L;
+    t.net.P = s->P; t.net.G = s->G; t.net.M = s->M; t.net.V = s->V;
+    t.net.Pb = s->Pb; t.net.Wf = s->Wf; t.net.Wt = s->Wt;
+    t.acts.rows = rows;
+    t.acts.colpart = s->part;
+    int64_t cp = 0;
+    int wgs = 0, bias = 0, frag = 0;
+    for (int l = 0; l <= L; ++l) {
+        const int M = s->lout[l], N = s->lin[l];
+        t.net.lin[l] = N;
+        t.net.lout[l] = M;
+        t.net.woff[l] = s->woff[l];
+        t.net.boff[l] = s->boff[l];
+        t.net.foff[l] = s->wfoff[l];
+        t.acts.in[l] = l == 0 ? s->X0 : s->Hb + (l - 1) * hsz;
+        t.acts.dz[l] = l == L ? s->dYb : s->dZb + l * hsz;
+        t.acts.dz32[l] = l == L ? s->dY : s->Z + l * hsz;
+        t.acts.cpoff[l] = cp;
+        cp += rows / COLSUM_ROWS * M;
+        t.dw.splits[l] = split_for(M, N, (int)rows);
+        t.dw.first[l] = wgs;
+        wgs += (M / DW_M) * (N >= DW_N ? N / DW_N : 1);
+        t.fin.bfirst[l] = bias;
+        bias += M / 64;
+    }
+    t.acts.losspart = s->part + cp;
+    t.dw.first[L + 1] = wgs;
+    t.fin.bfirst[L + 1] = frag = bias;
+    for (int l = 0; l <= L; ++l) {
+        const int M = s->lout[l], N = s->lin[l];
+        t.dw.cfirst[l] = wgs;
+        wgs += (int)(rows / COLSUM_ROWS) * (M > 512 ? M / 512 : 1);
+        t.fin.ffirst[l] = frag;
+        frag += (int)blocks((int64_t)M * N / 8, 256);
+    }
+    t.dw.cfirst[L + 1] = wgs;
+    t.fin.ffirst[L + 1] = frag;
+    t.fin.loss_wg = frag;
+    t.dw_wgs = wgs;
+    t.fin_wgs = frag + 1;
+    return t;
+}
+
+template <int H>
+hipError_t launch_train_rows(const TrainPlan &t, const sd::TrainBatch &b, hipStream_t st)
+{
+    using namespace sd;
+    const dim3 grid((unsigned)(t.acts.rows / TR_ROWS)), block(64 * RowGeo<H>::NW);
+    switch (t.net.depth) {
+    case 1: hipLaunchKernelGGL((train_rows_kernel<H, 1>), grid, block, 0, st, t.net, t.acts, b); break;
+    case 2: hipLaunchKernelGGL((train_rows_kernel<H, 2>), grid, block, 0, st, t.net, t.acts, b); break;
+    case 3: hipLaunchKernelGGL((train_rows_kernel<H, 3>), grid, block, 0, st, t.net, t.acts, b); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// One step on a batch: gradients and, with ad.on, Adam, the step counter and
+// the weights' fragment-order copies.
+hipError_t train_step(SeederState *s, const TrainPlan &t, const sd::TrainBatch &b, const sd::AdamArgs &ad,
+                      float *loss_out, hipStream_t st)
+{
+    using namespace sd;
+    hipError_t e = s->H == 128   ? launch_train_rows<128>(t, b, st)
+                   : s->H == 256 ? launch_train_rows<256>(t, b, st)
+                                 : launch_train_rows<512>(t, b, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(train_dw_kernel, dim3(t.dw_wgs), dim3(64 * DW_WAVES), 0, st, t.net, t.acts, t.dw, ad);
+    hipLaunchKernelGGL(train_finish_kernel, dim3(t.fin_wgs), dim3(256), 0, st, t.net, t.acts, t.fin, ad, s->dstep,
+                       loss_out);
+    return hipGetLastError();
+}
+
+// The weights' fragment-order copies from the BF16 parameters.
+hipError_t train_fragments(const TrainPlan &t, hipStream_t st)
+{
+    using namespace sd;
+    for (int l = 0; l <= t.net.depth; ++l) {
+        const int64_t pieces = (int64_t)t.net.lin[l] * t.net.lout[l] / 8;
+        hipLaunchKernelGGL(fragments_kernel, dim3(blocks(pieces, 256)), dim3(256), 0, st, t.net, l);
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 int seeder_infer_into(pk_ctx *ctx, int32_t id, const float *targets, int64_t T, float *seeds,
@@ -708,6 +816,14 @@ int pk_seeder_grad(pk_ctx *ctx, int32_t id, const float *x, const float *q, int6
     PK_HIP(ctx, hipSetDevice(ctx->device));
     int rc = alloc_acts(ctx, s, B);
     if (rc) return rc;
+    if (train_fused(s)) {
+        const TrainPlan t = train_plan(s, B);
+        const sd::TrainBatch b{x, q, s->n, 1, B, 0, nullptr, s->n, s->K};
+        PK_HIP(ctx, train_fragments(t, st));
+        PK_HIP(ctx, train_step(s, t, b, sd::AdamArgs{}, loss, st));
+        s->wf_dirty = false;
+        return PK_OK;
+    }
     hipLaunchKernelGGL(sd::load_rows_kernel, dim3(sd::blocks(B, 256)), dim3(256), 0, st, B, B, s->in_pad,
                        s->n, x, q, s->X0, s->Q);
     PK_HIP(ctx, hipGetLastError());
@@ -748,7 +864,19 @@ int pk_seeder_train(pk_ctx *ctx, int32_t id, const float *q_train, int64_t S, in
     }
     const int spe = (int)(S / batch);
     const int steps = spe * epochs;
-    for (int t = 0; t < steps && e == hipSuccess; ++t) {
+    const bool fused = train_fused(s);
+    if (fused && e == hipSuccess && steps > 0) {
+        const TrainPlan plan = train_plan(s, batch);
+        e = train_fragments(plan, st);
+        for (int t = 0; t < steps && e == hipSuccess; ++t) {
+            const int64_t ep = t / spe;
+            const sd::TrainBatch b{xall, q_train, 1, S, S, (int64_t)(t % spe) * batch,
+                                   perm ? perm + ep * S : nullptr, s->n, s->K};
+            const sd::AdamArgs ad{1, s->host_step + t, lr, 0.9f, 0.999f, 1e-8f};
+            e = train_step(s, plan, b, ad, loss_log ? loss_log + t : nullptr, st);
+        }
+    }
+    for (int t = 0; !fused && t < steps && e == hipSuccess; ++t) {
         hipLaunchKernelGGL(sd::gather_kernel, dim3(sd::blocks(batch, 256)), dim3(256), 0, st, batch, S, s->n,
                            s->in_pad, spe, steps, s->host_step, s->dstep, perm, xall, q_train, s->X0, s->Q);
         e = loss_and_grads(s, batch, batch, loss_log, s->host_step, steps, nullptr, st);
@@ -759,7 +887,7 @@ int pk_seeder_train(pk_ctx *ctx, int32_t id, const float *q_train, int64_t S, in
         e = hipGetLastError();
     }
     hipError_t e2 = hipStreamSynchronize(st);
-    s->wf_dirty = true;
+    s->wf_dirty = !fused || steps == 0 || e != hipSuccess || e2 != hipSuccess;
     (void)hipFree(pose);
     (void)hipFree(xall);
     if (e != hipSuccess) return fail(ctx, PK_EHIP, "pk_seeder_train: %s", hipGetErrorString(e));
