@@ -315,15 +315,17 @@ int alloc_acts(pk_ctx *ctx, SeederState *s, int64_t rows)
     ok &= hipMalloc(&s->dZ, hsz * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->dY, rows * s->out_pad * sizeof(float)) == hipSuccess;
     ok &= hipMalloc(&s->Q, rows * s->n * sizeof(float)) == hipSuccess;
-    // column-sum partials (one row per 128-row chunk) of every layer, loss partials (one per 16 rows)
-    ok &= hipMalloc(&s->part, ((rows / sd::COLSUM_ROWS + 1) * (size_t)(L * s->H + s->out_pad) +
-                               rows / 16 + 1) * sizeof(float) + 4096) == hipSuccess;
+    // column-sum partials (four per 128-row chunk) of every layer, the rows' losses
+    ok &= hipMalloc(&s->part, ((rows / sd::COLSUM_ROWS + 1) * (size_t)4 * (L * s->H + s->out_pad) + rows) *
+                                  sizeof(float) + 4096) == hipSuccess;
     // Split-K partials: sized for the largest split any row count can pick.
     size_t need = 0;
     for (int l = 0; l <= L; ++l) {
         const int M = s->lout[l], N = s->lin[l];
         need = std::max(need, (size_t)sd::split_max(M, N) * M * N);
     }
+    need = std::max(need, (size_t)sd::split_max(s->out_pad, s->H) * s->out_pad * s->H +
+                              (size_t)sd::split_max(s->H, s->in_pad) * s->H * s->in_pad);
     if (s->splitbuf) (void)hipFree(s->splitbuf);
     s->splitbuf = nullptr;
     s->splitbuf_floats = 0;
@@ -660,7 +662,7 @@ TrainPlan train_plan(SeederState *s, int64_t rows)
     t.acts.rows = rows;
     t.acts.colpart = s->part;
     int64_t cp = 0;
-    int wgs = 0, bias = 0, frag = 0;
+    int wgs = 0, bias = 0;
     for (int l = 0; l <= L; ++l) {
         const int M = s->lout[l], N = s->lin[l];
         t.net.lin[l] = N;
@@ -670,30 +672,27 @@ TrainPlan train_plan(SeederState *s, int64_t rows)
         t.net.foff[l] = s->wfoff[l];
         t.acts.in[l] = l == 0 ? s->X0 : s->Hb + (l - 1) * hsz;
         t.acts.dz[l] = l == L ? s->dYb : s->dZb + l * hsz;
-        t.acts.dz32[l] = l == L ? s->dY : s->Z + l * hsz;
         t.acts.cpoff[l] = cp;
-        cp += rows / COLSUM_ROWS * M;
+        cp += rows / COLSUM_ROWS * 4 * M;
         t.dw.splits[l] = split_for(M, N, (int)rows);
-        t.dw.first[l] = wgs;
-        wgs += (M / DW_M) * (N >= DW_N ? N / DW_N : 1);
         t.fin.bfirst[l] = bias;
         bias += M / 64;
     }
-    t.acts.losspart = s->part + cp;
-    t.dw.first[L + 1] = wgs;
-    t.fin.bfirst[L + 1] = frag = bias;
-    for (int l = 0; l <= L; ++l) {
-        const int M = s->lout[l], N = s->lin[l];
-        t.dw.cfirst[l] = wgs;
-        wgs += (int)(rows / COLSUM_ROWS) * (M > 512 ? M / 512 : 1);
-        t.fin.ffirst[l] = frag;
-        frag += (int)blocks((int64_t)M * N / 8, 256);
+    t.acts.rowloss = s->part + cp;
+    for (int l = 1; l < L; ++l) {
+        t.dw.tile_first[l] = wgs;
+        wgs += (s->lout[l] / DW_M) * (s->lin[l] / DW_N);
     }
-    t.dw.cfirst[L + 1] = wgs;
-    t.fin.ffirst[L + 1] = frag;
-    t.fin.loss_wg = frag;
-    t.dw_wgs = wgs;
-    t.fin_wgs = frag + 1;
+    t.dw.tile_first[L > 1 ? L : 1] = t.dw.tiles = wgs;
+    t.dw.units = t.dw.splits[L] * (s->lout[L] / DW_M) * (s->lin[L] / DW_N) + t.dw.splits[0] * (s->lout[0] / DW_M);
+    t.dw.part = s->splitbuf;
+    t.dw.part0 = (int64_t)t.dw.splits[L] * s->lout[L] * s->lin[L];
+    t.dw_wgs = std::max(wgs, std::min(256, (t.dw.units + DW_WAVES - 1) / DW_WAVES));
+    t.dw_wgs = (t.dw_wgs + 7) / 8 * 8;
+    t.fin.bfirst[L + 1] = t.fin.wfirst = bias;
+    t.fin.w0first = bias + (int)blocks((int64_t)s->lout[L] * s->lin[L], 1024);
+    t.fin.loss_wg = t.fin.w0first + (int)blocks((int64_t)s->lout[0] * s->lin[0], 1024);
+    t.fin_wgs = t.fin.loss_wg + 1;
     return t;
 }
 
@@ -722,8 +721,8 @@ hipError_t train_step(SeederState *s, const TrainPlan &t, const sd::TrainBatch &
                                  : launch_train_rows<512>(t, b, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(train_dw_kernel, dim3(t.dw_wgs), dim3(64 * DW_WAVES), 0, st, t.net, t.acts, t.dw, ad);
-    hipLaunchKernelGGL(train_finish_kernel, dim3(t.fin_wgs), dim3(256), 0, st, t.net, t.acts, t.fin, ad, s->dstep,
-                       loss_out);
+    hipLaunchKernelGGL(train_finish_kernel, dim3(t.fin_wgs), dim3(256), 0, st, t.net, t.acts, t.dw, t.fin, ad,
+                       s->dstep, loss_out);
     return hipGetLastError();
 }
 
