@@ -49,9 +49,11 @@ template <int NJ>
 struct TrajLds {
     static constexpr int HB = 4 * NJ, W = HB + 1;
     static constexpr int NPAIR = HB * (HB + 1) / 2;
-    double band[TRAJ_VMAX * W];
     double b[TRAJ_VMAX];
     double invd[TRAJ_VMAX];                            // 1 / D_j of the L D L^T factorisation
+    double dump[64];                                   // where masked stores go
+    static constexpr int NX = (NJ + 1) / 2 * 2;
+    double next[(NJ + 1) * NX];                        // the next block's rows of the block just eliminated (+ dump row)
     float Q[TRAJ_VMAX], Qt[TRAJ_VMAX];
     float J0[6 * NJ], J1[6 * NJ], r0[6], r1[6];        // pose rows at the current point
     float Jt0[6 * NJ], Jt1[6 * NJ], rt0[6], rt1[6];    // ... at the trial point
@@ -65,6 +67,10 @@ struct TrajLds {
     double ctab[5 * (TRAJ_VMAX / NJ)];
     float racc[TRAJ_VMAX], rjerk[TRAJ_VMAX];          // stencil rows at the current point
     int fail;                                          // a pivot failed in the factorisation
+    // A(v, v - k) at v * W + k.  The factorisation reads some entries beside
+    // the band before it discards them: up to 64 past its end, and up to 16
+    // rows before its start (the arrays above).
+    double band[TRAJ_VMAX * W + 64];
 };
 
 PK_DEV float wsum(float v)
@@ -307,16 +313,13 @@ PK_DEV void form_system(const RobotC *__restrict__ rb, const TrajParams &P, Traj
     }
 }
 
-// The trailing triangle of a block step at c0: entries (R, R2) =
-// (c0 + NJ - 1 + di, c0 + NJ - 1 + dk), 1 <= dk <= di <= HB, in two parts:
-// A (dk <= NJ: the next block's columns, which its elimination needs) and B
-// (dk > NJ).  A is spread over the workgroup, B over wavefronts 1..3.
+// The part of a block step's trailing triangle beyond the next block's
+// columns: entries (R, R2) = (c0 + NJ - 1 + di, c0 + NJ - 1 + dk) with
+// NJ < dk <= di <= HB, spread over wavefronts 1..3.
 template <int NJ>
 struct Pairs {
     static constexpr int HB = TrajLds<NJ>::HB;
-    static constexpr int NA = NJ * (HB + 1) - NJ * (NJ + 1) / 2;
     static constexpr int NB = (HB - NJ) * (HB - NJ + 1) / 2;
-    static constexpr int PA = (NA + TRAJ_THREADS - 1) / TRAJ_THREADS;
     static constexpr int PB = (NB + TRAJ_THREADS - 64 - 1) / (TRAJ_THREADS - 64);
 };
 
@@ -406,141 +409,180 @@ PK_DEV double recip(double d)
     return fma(r, fma(-d, r, 1.0), r);
 }
 
-// In-place band L D L^T factorisation of band (half-bandwidth HB, unit L)
-// and the solve of L D L^T x = rhs (x over rhs).  A pivot D_j not above
-// thresh_rel times the largest damped diagonal fails the factorisation
-// (returns false).
-//
-// No square roots; blocked by timestep: after the factorisation band[j * W]
-// holds D_j and band[i * W + (i - j)] the unscaled entry D_j L_ij, with
-// invd[j] = 1 / D_j.  Each block step of NJ columns eliminates its window
-// (the block's rows and the HB rows below it, at most 64) on the first
-// wavefront in registers, carrying the right-hand side along as one more
-// column (the forward substitution L y = rhs); then all threads apply the
-// part of the block's rank-NJ trailing update that falls in the next block's
-// columns, and the rest of it runs on wavefronts 1..3 while wavefront 0
-// eliminates the next block (look-ahead: the two touch disjoint entries).
-// Two workgroup barriers per NJ columns.  The backward solve L^T x = D^-1 y
-// runs on the first wavefront with the vector in registers (lane l holds
-// entries l, l + 64, ...): per chunk of CH steps the lanes read their
-// coefficients at once, then each step broadcasts the finished entry with
-// readlane and the lanes holding the previous HB entries take their update,
-// with no memory access or branch on that dependent chain.
-template <int NJ, typename T>
-PK_DEV bool band_solve(T *band, T *rhs, T *invd, int V, float thresh_rel,
-                       const int (&mpa)[Pairs<NJ>::PA], const int (&mpb)[Pairs<NJ>::PB], int lane,
-                       float *red, int *fail)
+// Columns c0 .. c0 + NJ - 1 of the factor scaled by 1 / D (wavefronts 1..3,
+// thread t of them).
+template <int NJ>
+PK_DEV void scale_columns(double *band, const double *invd, int V, int c0, int t)
 {
     constexpr int HB = TrajLds<NJ>::HB, W = TrajLds<NJ>::W;
-    constexpr int NS = TRAJ_VMAX / 64, CH = 8, NR = NJ + HB;
-    static_assert(NR <= 64, "a block step's window fits one wavefront");
-    float mx = 0.f;
-    for (int v = lane; v < V; v += TRAJ_THREADS) mx = fmaxf(mx, (float)band[v * W]);
-    const T thresh = (T)thresh_rel * (T)block_max(mx, red);
-    if (lane == 0) *fail = 0;
-    for (int c0 = 0; c0 < V; c0 += NJ) {
-        // Block step over columns c0 .. c0 + NJ - 1.  Lane r of the first
-        // wavefront holds row R = c0 + r of the window (the block's rows
-        // and the HB rows below) restricted to the block's columns, x[cc]
-        // = A(R, c0 + cc), 0 outside the band; the NJ elimination steps run
-        // in registers, each broadcasting its pivot row's column with
-        // readlane.
-        if (lane >= 64) {
-            // meanwhile: part B of the previous block (entries beyond this
-            // block's columns, which the elimination does not touch)
-            if (c0 > 0) trail<NJ, T>(band, invd, V, c0 - NJ, mpb);
-        } else {
-            const int R = c0 + lane;
-            const bool live = lane < NR && R < V;
-            T x[NJ];
 #pragma unroll
-            for (int cc = 0; cc < NJ; ++cc) {
-                const int k = R - (c0 + cc);
-                x[cc] = live && k >= 0 && k <= HB ? band[R * W + k] : (T)0;
-            }
-            T bv = live ? rhs[R] : (T)0;   // right-hand side as one more column
-            bool bad = false;
+    for (int e0 = 0; e0 < NJ * HB; e0 += TRAJ_THREADS - 64) {
+        const int e = e0 + t, cc = e / HB, k = e % HB + 1, R = c0 + cc + k;
+        if (e < NJ * HB && R < V) band[R * W + k] *= invd[c0 + cc];
+    }
+}
+
+// In-place band L D L^T factorisation of S.band (half-bandwidth HB, unit L)
+// and the solve of L D L^T x = rhs (x over S.b).  A pivot D_j not above
+// thresh_rel times the largest damped diagonal fails the factorisation
+// (returns false).  No square roots.
+//
+// Bound: the dependent chain of pivots, so the first wavefront runs it with
+// as little in between as possible: no branches (a masked store goes to the
+// lane's own slot of a dump) and one workgroup barrier per block of NJ
+// columns.  Row R lives in lane R mod 64 while it is
+// in the window of a block (the block's rows and the HB rows below),
+// restricted to the block's columns, with the right-hand side as one more
+// column (the forward substitution).  Per block the first wavefront
+//   * eliminates the NJ columns in registers, broadcasting each pivot row's
+//     entries with readlane, and stores them (unscaled entries D_j L_ij);
+//   * after the barrier applies the rank-NJ update to the next block's
+//     columns in registers, the multiplying rows read back from LDS by every
+//     lane alike (the loads issued before the barrier; by readlane this phase
+//     took twice as long),
+// while wavefronts 1..3 apply the rest of the block's update to the columns
+// beyond (disjoint entries) and scale finished columns by 1 / D_j.
+// The backward solve L^T x = D^-1 y runs on the first wavefront with row i in
+// lane i mod 64 (a finished entry reaches the HB rows above it only): per
+// step one readlane pair and one FMA depend on the step before.
+// With two barriers per block, the next block's columns updated through LDS
+// by the whole workgroup and two register slots per lane in the backward
+// solve, 1024 trajectories of 32 x 7 variables took 3.10 ms and 37 of 25 x 6
+// (one workgroup's time) 0.979 ms; now 2.74 and 0.809.
+template <int NJ>
+PK_DEV bool band_solve(TrajLds<NJ> &S, int V, float thresh_rel, const int (&mpb)[Pairs<NJ>::PB], int tid)
+{
+    constexpr int HB = TrajLds<NJ>::HB, W = TrajLds<NJ>::W, NR = NJ + HB, NX = TrajLds<NJ>::NX, CH = 16;
+    static_assert(NR + NJ <= 64, "the windows of a block and the next fit one wavefront");
+    static_assert(HB + CH < 64, "a finished row's lane takes its next row before that is updated");
+    double *band = S.band, *rhs = S.b, *invd = S.invd;
+    float mx = 0.f;
+    for (int v = tid; v < V; v += TRAJ_THREADS) mx = fmaxf(mx, (float)band[v * W]);
+    const double thresh = (double)thresh_rel * (double)block_max(mx, S.red);
+    if (tid == 0) S.fail = 0;
+    // (a scalar branch: every wavefront passes one barrier per block)
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) != 0) {
+        for (int c0 = 0; c0 < V; c0 += NJ) {
+            __syncthreads();
+            trail<NJ, double>(band, invd, V, c0, mpb);
+            if (c0 > 0) scale_columns<NJ>(band, invd, V, c0 - NJ, tid - 64);
+        }
+        scale_columns<NJ>(band, invd, V, V - NJ, tid - 64);
+    } else {
+        const int lane = tid, dump = (int)(&S.dump[lane] - band);   // as an index of the band
+        bool bad = false;
+        double x[NJ], bv;
+#pragma unroll
+        for (int cc = 0; cc < NJ; ++cc) {
+            const bool ok = (unsigned)(lane - cc) <= (unsigned)HB && lane < V;
+            const double v = band[ok ? lane * W + lane - cc : 0];
+            x[cc] = ok ? v : 0.0;
+        }
+        bv = rhs[min(lane, V - 1)];
+        for (int c0_ = 0; c0_ < V; c0_ += NJ) {
+            // (opaque and uniform: addresses are formed per block, not carried)
+            const int c0 = __builtin_amdgcn_readfirstlane(c0_);
+            const int r = (lane - c0) & 63, R = c0 + r;
+            double inv[NJ];
 #pragma unroll
             for (int jj = 0; jj < NJ; ++jj) {
                 // a failed pivot discards the whole factorisation, so the
                 // test stays off the dependent chain
-                const T d = readlane_d(x[jj], jj);
-                bad |= !(d > thresh) || !(d < (T)INFINITY);
-                const T inv = recip(d);
-                if (lane == 0) invd[c0 + jj] = inv;
-                const T ell = lane > jj ? x[jj] : (T)0;   // unscaled D_jj L_(R, jj)
+                const int pl = (c0 + jj) & 63;
+                const double d = readlane_d(x[jj], pl);
+                bad |= !(d > thresh) || !(d < (double)INFINITY);
+                inv[jj] = recip(d);
+                const double ell = r > jj ? x[jj] : 0.0;   // unscaled D_jj L_(R, jj)
 #pragma unroll
-                for (int cc = jj + 1; cc < NJ; ++cc) x[cc] -= ell * (readlane_d(x[jj], cc) * inv);
-                bv -= ell * (readlane_d(bv, jj) * inv);
+                for (int cc = jj + 1; cc < NJ; ++cc)
+                    x[cc] -= ell * (readlane_d(x[jj], (c0 + cc) & 63) * inv[jj]);
+                bv -= ell * (readlane_d(bv, pl) * inv[jj]);
+            }
+            {   // the next block's rows, for every lane to read back
+                const int n = r >= NJ && r < 2 * NJ ? r - NJ : NJ;
+#pragma unroll
+                for (int cc = 0; cc < NJ; ++cc) S.next[n * NX + cc] = x[cc];
+            }
+            const int rw = R < V ? r : 127;            // rows past the end store nothing
+#pragma unroll
+            for (int cc = 0; cc < NJ; ++cc)
+                band[(unsigned)(rw - cc) <= (unsigned)HB ? R * W + r - cc : dump] = x[cc];
+            double iv = inv[0];
+#pragma unroll
+            for (int jj = 1; jj < NJ; ++jj) iv = r == jj ? inv[jj] : iv;
+            invd[r < NJ ? R : TRAJ_VMAX + lane] = iv;              // (else the dump, which follows)
+            rhs[r < NJ ? R : 2 * TRAJ_VMAX + lane] = bv;
+            double a2[NJ][NX];
+#pragma unroll
+            for (int i = 0; i < NJ; ++i)
+#pragma unroll
+                for (int cc = 0; cc < NX; ++cc) a2[i][cc] = S.next[i * NX + cc];
+            __builtin_amdgcn_sched_barrier(0);         // (all in flight, not one by one where they are used)
+            __syncthreads();
+            if (c0 + NJ >= V) break;
+            // the next block's columns: rows R1 (this lane) x c0 + NJ + i
+            const int r1 = (lane - c0 - NJ) & 63, R1 = min(c0 + NJ + r1, V - 1);
+            double tv[NJ], m[NJ];
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) tv[i] = band[R1 * W + r1 - i];   // (in S where not in the band)
+            const double bn = rhs[R1];
+            bv = r1 >= NR - NJ ? bn : bv;              // rows entering the window
+#pragma unroll
+            for (int cc = 0; cc < NJ; ++cc) m[cc] = x[cc] * inv[cc];
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) {
+                double term[NJ];
+#pragma unroll
+                for (int cc = 0; cc < NJ; ++cc) term[cc] = m[cc] * a2[i][cc];
+                // pairwise sum: a short dependent chain
+#pragma unroll
+                for (int w = 1; w < NJ; w *= 2)
+#pragma unroll
+                    for (int cc = 0; cc + w < NJ; cc += 2 * w) term[cc] += term[cc + w];
+                tv[i] -= term[0];
             }
 #pragma unroll
-            for (int cc = 0; cc < NJ; ++cc) {
-                const int k = R - (c0 + cc);
-                if (live && k >= 0 && k <= HB) band[R * W + k] = x[cc];
-            }
-            if (live) rhs[R] = bv;
-            if (bad && lane == 0) *fail = 1;
+            for (int i = 0; i < NJ; ++i) x[i] = (unsigned)(r1 - i) <= (unsigned)HB ? tv[i] : 0.0;
         }
-        __syncthreads();
-        trail<NJ, T>(band, invd, V, c0, mpa);   // part A of this block
-        __syncthreads();
+        if (bad && lane == 0) S.fail = 1;
     }
-    if (*fail) return false;
-    // rhs now holds y of L y = rhs (forward substitution rode along with the
-    // elimination)
-    if (lane < 64) {
-        T x[NS];
+    __syncthreads();
+    if (S.fail) return false;
+    // S.b now holds y of L y = rhs (forward substitution rode along with the
+    // elimination), S.band L
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+        const int lane = tid;
+        // row i of the 64 up to j: i = j - ((j - lane) mod 64); D z = y
+        auto row = [&](int i) { return i >= 0 ? rhs[max(i, 0)] * invd[max(i, 0)] : 0.0; };
+        double x = row(V - 1 - ((V - 1 - lane) & 63));
+        double c[CH], cn[CH];
+        // entries L(j0 - u, row of this lane), 0 outside the band: every load
+        // at its place on the row's diagonal, then the selects
+        auto load = [&](double(&o)[CH], int j0) {
+            const int k0 = (j0 - lane) & 63, kk = k0 <= j0 ? k0 : -1;
+            const double *p = band + max(j0, 0) * W + k0;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int i = 64 * s + lane;
-            x[s] = i < V ? rhs[i] : (T)0;
-        }
-        // D z = y
+            for (int u = 0; u < CH; ++u) o[u] = p[-u * (W + 1)];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int i = 64 * s + lane;
-            if (i < V) x[s] *= invd[i];
-        }
-        // L^T x = z: the entry finished at step j updates i in [j - HB, j)
-        // by -L_ji x_j; the candidate i sits in slot s when lane < j % 64
-        // (cs), else in slot s - 1 (cp).
+            for (int u = 0; u < CH; ++u) o[u] = (unsigned)(kk - u - 1) < (unsigned)HB ? o[u] : 0.0;
+        };
+        load(c, V - 1);
+        for (int j0_ = V - 1; j0_ >= 0; j0_ -= CH) {
+            const int j0 = __builtin_amdgcn_readfirstlane(j0_);
+            const int q = (j0 - lane) & 63, i = j0 - q;
+            const double z = row(i - 64);
+            load(cn, j0 - CH);
 #pragma unroll
-        for (int s = NS - 1; s >= 0; --s) {
-#pragma unroll 1
-            for (int l0 = 64 - CH; l0 >= 0; l0 -= CH) {
-                const int jt = 64 * s + l0;
-                if (jt >= V) continue;
-                T cs[CH], cp[CH];
-#pragma unroll
-                for (int u = 0; u < CH; ++u) {   // loads first, all in flight together
-                    const int l = l0 + CH - 1 - u, j = 64 * s + l;
-                    const int i = 64 * s + lane - (lane < l ? 0 : 64);
-                    const bool ok = j < V && i >= 0 && j - i <= HB;
-                    cs[u] = band[ok ? j * W + (j - i) : 0];
-                    cp[u] = invd[ok ? i : 0];
-                }
-#pragma unroll
-                for (int u = 0; u < CH; ++u) {
-                    const int l = l0 + CH - 1 - u, j = 64 * s + l;
-                    const bool dn = lane < l;
-                    const int i = 64 * s + lane - (dn ? 0 : 64);
-                    const bool ok = j < V && i >= 0 && j - i <= HB;
-                    const T c = cs[u] * cp[u];
-                    cs[u] = ok && dn ? c : (T)0;
-                    cp[u] = ok && !dn ? c : (T)0;
-                }
-#pragma unroll
-                for (int u = 0; u < CH; ++u) {
-                    const T y = readlane_d(x[s], l0 + CH - 1 - u);
-                    x[s] -= cs[u] * y;
-                    if (s > 0) x[s - 1] -= cp[u] * y;
-                }
+            for (int u = 0; u < CH; ++u) {
+                const double y = readlane_d(x, (j0 - u) & 63);
+                x -= c[u] * y;
             }
-        }
+            // the chunk's rows are finished; their lanes take the rows 64 above
+            rhs[q < CH && i >= 0 ? i : 2 * TRAJ_VMAX + lane] = x;
+            x = q < CH ? z : x;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int i = 64 * s + lane;
-            if (i < V) rhs[i] = x[s];
+            for (int u = 0; u < CH; ++u) c[u] = cn[u];
         }
     }
     __syncthreads();
@@ -559,8 +601,7 @@ __global__ __launch_bounds__(TRAJ_THREADS, NJ <= 7 ? 2 : 1) void traj_kernel(con
     const int64_t b = blockIdx.x;
     if (b >= P.B) return;   // uniform per workgroup
     const int TT = P.T, V = TT * NJ;
-    int mpa[Pairs<NJ>::PA], mpb[Pairs<NJ>::PB];
-    part_pairs<NJ>(lane, TRAJ_THREADS, 1, Pairs<NJ>::NA, mpa);
+    int mpb[Pairs<NJ>::PB];
     part_pairs<NJ>(lane - 64, TRAJ_THREADS - 64, NJ + 1, Pairs<NJ>::NB, mpb);
     const float *src = P.init + b * (int64_t)V;
     for (int v = lane; v < V; v += TRAJ_THREADS) S.Q[v] = src[v];
@@ -665,8 +706,7 @@ __global__ __launch_bounds__(TRAJ_THREADS, NJ <= 7 ? 2 : 1) void traj_kernel(con
         // rejected trial, as when the IK re-solve fails)
         form_system<NJ, double>(rb, P, S, lam, lane, S.band, S.b);
         __syncthreads();
-        const bool ok =
-            band_solve<NJ, double>(S.band, S.b, S.invd, V, P.pivot_rel, mpa, mpb, lane, S.red, &S.fail);
+        const bool ok = band_solve<NJ>(S, V, P.pivot_rel, mpb, lane);
         for (int v = lane; v < V; v += TRAJ_THREADS) S.Qt[v] = S.Q[v] + (ok ? (float)S.b[v] : 0.f);
         evaluate = ok;
         __syncthreads();
