@@ -223,7 +223,8 @@ PK_DEV void eval_jacobian_chain(const RobotC *__restrict__ rb, const SolveParams
         const float over = q[j] - rb->j[j].hi, under = rb->j[j].lo - q[j];
         const float rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
         const float rr = P.w_rest * (q[j] - qr[j]);
-        const float dl = over > 0.f ? P.w_limit : (under > 0.f ? -P.w_limit : 0.f);
+        const float wl = P.w_limit;
+        const float dl = over > 0.f ? wl : (under > 0.f ? -wl : 0.f);
         S[SL::DG + j] = dl * dl + P.w_rest * P.w_rest;
         S[SL::GX + j] = dl * rl + P.w_rest * rr;
     }
@@ -237,7 +238,9 @@ PK_DEV void joint_terms_at(const SolveParams &P, float q, float lo, float hi, fl
     const float over = q - hi, under = lo - q;
     const float rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
     const float rr = P.w_rest * (q - qr);
-    const float dl = over > 0.f ? P.w_limit : (under > 0.f ? -P.w_limit : 0.f);
+    // (the weight in a register first: loaded in the arms it made two branches per joint)
+    const float wl = P.w_limit;
+    const float dl = over > 0.f ? wl : (under > 0.f ? -wl : 0.f);
     dg = dl * dl + P.w_rest * P.w_rest;
     gx = dl * rl + P.w_rest * rr;
 }

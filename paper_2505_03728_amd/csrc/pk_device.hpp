@@ -151,10 +151,11 @@ PK_DEV void rot_to_quat(const float *R, float &w, float &x, float &y, float &z)
     const bool c0 = tr >= R[0] && tr >= R[4] && tr >= R[8];
     const bool c1 = !c0 && R[0] >= R[4] && R[0] >= R[8];
     const bool c2 = !c0 && !c1 && R[4] >= R[8];
-    const float t = c0 ? 1.f + tr
-                  : c1 ? 1.f + R[0] - R[4] - R[8]
-                  : c2 ? 1.f + R[4] - R[0] - R[8]
-                       : 1.f + R[8] - R[0] - R[4];
+    // (all four formed: as arms of the selects they were sunk into branches)
+    float t0 = 1.f + tr, t1 = 1.f + R[0] - R[4] - R[8], t2 = 1.f + R[4] - R[0] - R[8],
+          t3 = 1.f + R[8] - R[0] - R[4];
+    asm("" : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3));
+    const float t = c0 ? t0 : c1 ? t1 : c2 ? t2 : t3;
     const float s = 2.f * sqrtf(t), is = rcp(s), big = 0.25f * s;
     const float d1 = (R[7] - R[5]) * is, d2 = (R[2] - R[6]) * is, d3 = (R[3] - R[1]) * is;
     const float s1 = (R[1] + R[3]) * is, s2 = (R[2] + R[6]) * is, s3 = (R[5] + R[7]) * is;
@@ -164,7 +165,11 @@ PK_DEV void rot_to_quat(const float *R, float &w, float &x, float &y, float &z)
     x = c0 ? d1 : c1 ? big : c2 ? s1 : s2;
     y = c0 ? d2 : c1 ? s1 : c2 ? big : s3;
     z = c0 ? d3 : c1 ? s2 : c2 ? s3 : big;
-    if (w < 0.f) { w = -w; x = -x; y = -y; z = -z; }
+    const bool neg = w < 0.f;
+    w = neg ? -w : w;
+    x = neg ? -x : x;
+    y = neg ? -y : y;
+    z = neg ? -z : z;
     float in = rsqrtf(w * w + x * x + y * y + z * z);
     w *= in; x *= in; y *= in; z *= in;
 }
@@ -186,7 +191,20 @@ struct PoseLog {
     float sh, ch;      // sin(theta/2), cos(theta/2)
 };
 
-// log of the pose (RE, tE).
+// k = (1 - (theta/2) cot(theta/2)) / theta^2, cot(theta/2) = w / s (s, w: sine
+// and cosine of theta/2); a series where that cancels.
+PK_DEV float jl_inv_k(float theta, float s, float w)
+{
+    const float t2 = theta * theta;
+    const float k0 = 1.f / 12.f + t2 * (1.f / 720.f + t2 * (1.f / 30240.f));
+    const float k1 = (1.f - 0.5f * theta * w * rcp(s)) * rcp(t2);
+    return theta < 0.1f ? k0 : k1;
+}
+
+// log of the pose (RE, tE).  Both forms of each switch here, in jl_inv_k and
+// in jr_coef are computed and one selected: a wavefront nearly always has
+// lanes on either side, and as branches the switches cut the code into small
+// blocks that each waited for their masks.
 PK_DEV PoseLog pose_log_of(const float *RE, const float *tE)
 {
     PoseLog L;
@@ -195,19 +213,16 @@ PK_DEV PoseLog pose_log_of(const float *RE, const float *tE)
     float s = sqrtf(x * x + y * y + z * z);
     float theta = 2.f * atan2f(s, w);
     // phi = theta * v / |v|;  theta / s -> 2 / w (1 - s^2 / (3 w^2)) as s -> 0.
-    const float iw = rcp(w);
-    float f = s < 1e-4f ? 2.f * iw * (1.f - (1.f / 3.f) * s * s * iw * iw) : theta * rcp(s);
+    const float iw = rcp(w), is = rcp(s);
+    const float f0 = 2.f * iw * (1.f - (1.f / 3.f) * s * s * iw * iw), f1 = theta * is;
+    const float f = s < 1e-4f ? f0 : f1;
     L.phi[0] = f * x; L.phi[1] = f * y; L.phi[2] = f * z;
     L.theta = theta;
     L.sh = s;
     L.ch = w;
     // rho = J_l^-1(phi) t_E = t_E - phi x t_E / 2 + k phi x (phi x t_E),
-    // k = (1 - (theta/2) cot(theta/2)) / theta^2, cot(theta/2) = w / s.
-    float t2 = theta * theta, k;
-    if (theta < 0.1f)
-        k = 1.f / 12.f + t2 * (1.f / 720.f + t2 * (1.f / 30240.f));
-    else
-        k = (1.f - 0.5f * theta * w * rcp(s)) * rcp(t2);
+    // k = jl_inv_k.
+    const float k = jl_inv_k(theta, s, w);
     float a[3], b[3];
     cross(L.phi, tE, a);
     cross(L.phi, a, b);
@@ -246,23 +261,17 @@ struct JrCoef {
 PK_DEV JrCoef jr_coef(const PoseLog &L)
 {
     JrCoef J;
-    const float th = L.theta, t2 = th * th;
-    float k, a1, a2, a3;
-    if (th < 0.1f)
-        k = 1.f / 12.f + t2 * (1.f / 720.f + t2 * (1.f / 30240.f));
-    else
-        k = (1.f - 0.5f * th * L.ch * rcp(L.sh)) * rcp(t2);
-    if (th < 0.5f) {
-        a1 = 1.f / 6.f + t2 * (-1.f / 120.f + t2 * (1.f / 5040.f - t2 * (1.f / 362880.f)));
-        a2 = 1.f / 24.f + t2 * (-1.f / 720.f + t2 * (1.f / 40320.f - t2 * (1.f / 3628800.f)));
-        a3 = 1.f / 120.f + t2 * (-1.f / 2520.f + t2 * (1.f / 120960.f - t2 * (1.f / 9979200.f)));
-    } else {
-        const float st = 2.f * L.sh * L.ch, ct = L.ch * L.ch - L.sh * L.sh;
-        const float it = rcp(th), it2 = it * it, it3 = it2 * it;
-        a1 = (th - st) * it3;
-        a2 = (t2 - 4.f * L.sh * L.sh) * (0.5f * it2 * it2);   // 2 cos - 2 = -4 sin^2(th/2)
-        a3 = (2.f * th - 3.f * st + th * ct) * (0.5f * it3 * it2);
-    }
+    const float th = L.theta, t2 = th * th, k = jl_inv_k(th, L.sh, L.ch);
+    const float s1 = 1.f / 6.f + t2 * (-1.f / 120.f + t2 * (1.f / 5040.f - t2 * (1.f / 362880.f)));
+    const float s2 = 1.f / 24.f + t2 * (-1.f / 720.f + t2 * (1.f / 40320.f - t2 * (1.f / 3628800.f)));
+    const float s3 = 1.f / 120.f + t2 * (-1.f / 2520.f + t2 * (1.f / 120960.f - t2 * (1.f / 9979200.f)));
+    const float st = 2.f * L.sh * L.ch, ct = L.ch * L.ch - L.sh * L.sh;
+    const float it = rcp(th), it2 = it * it, it3 = it2 * it;
+    const float l1 = (th - st) * it3;
+    const float l2 = (t2 - 4.f * L.sh * L.sh) * (0.5f * it2 * it2);   // 2 cos - 2 = -4 sin^2(th/2)
+    const float l3 = (2.f * th - 3.f * st + th * ct) * (0.5f * it3 * it2);
+    const bool series = th < 0.5f;
+    const float a1 = series ? s1 : l1, a2 = series ? s2 : l2, a3 = series ? s3 : l3;
     const float *f = L.phi, *r = L.rho;
     const float d = f[0] * r[0] + f[1] * r[1] + f[2] * r[2];
     const float ff2 = f[0] * f[0] + f[1] * f[1] + f[2] * f[2];   // t2 of the identities

@@ -169,7 +169,8 @@ PK_DEV void limit_row(const TrajLds<NJ> &S, const TrajParams &P, float q, int i,
 {
     const float over = q - S.hi[i], under = S.lo[i] - q;
     rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
-    dl = over > 0.f ? P.w_limit : (under > 0.f ? -P.w_limit : 0.f);
+    const float wl = P.w_limit;
+    dl = over > 0.f ? wl : (under > 0.f ? -wl : 0.f);
 }
 
 template <int NJ>
