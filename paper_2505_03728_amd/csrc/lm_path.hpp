@@ -287,8 +287,7 @@ PK_DEV void point(const SolveParams &P, const LaneInfo<DMAX> &I, int lane, int m
         const float over = q - I.hi, under = I.lo - q;
         X.rl = P.w_limit * (fmaxf(over, 0.f) + fmaxf(under, 0.f));
         X.rr = P.w_rest * (q - I.qr);
-        const float wl = P.w_limit;
-        X.dl = over > 0.f ? wl : (under > 0.f ? -wl : 0.f);
+        X.dl = over > 0.f ? P.w_limit : (under > 0.f ? -P.w_limit : 0.f);
         jcost = X.rl * X.rl + X.rr * X.rr;
     }
     X.pcost = wave_sum(ecost);

@@ -112,9 +112,10 @@ struct Lane {
     float lo[Geo<L, KIND>::NS], hi[Geo<L, KIND>::NS], qr[Geo<L, KIND>::NS];
     bool pris[Geo<L, KIND>::NS];
     float tp, Rt[3];                        // target position's component, column `row` of its rotation
-    // Joint and EE transforms (G, then t).  Read with scalar loads where they
+    // The own row of the first joint's transform, the others and the EE's whole
+    // (G, then t).  Read with scalar loads where they
     // are used, each joint's wait for them stood in the one wavefront's way.
-    float fr[L + 1][12];
+    float g0[3], t0, fr[L][12];
     float *ex;                              // the problem's exchange area
 };
 
@@ -200,13 +201,15 @@ PK_DEV bool eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
         }
     }
     // forward kinematics, row by row
-    float o[3], p = 0.f;
-#pragma unroll
-    for (int u = 0; u < 3; ++u) o[u] = Q.row == u ? 1.f : 0.f;
+    float o[3], p;
 #pragma unroll
     for (int j = 0; j < L; ++j) {
-        float on[3], pn;
-        joint_step_row(o, p, Q.fr[j], Q.fr[j] + 9, from(so[j / 4], j % 4), from(co[j / 4], j % 4), on, pn);
+        float on[3], pn = Q.t0;
+        const float s = from(so[j / 4], j % 4), c = from(co[j / 4], j % 4);
+        if (j == 0)
+            joint_turn_row(Q.g0[0], Q.g0[1], Q.g0[2], s, c, on);   // (the identity times it)
+        else
+            joint_step_row(o, p, Q.fr[j - 1], Q.fr[j - 1] + 9, s, c, on, pn);
         if (pris_of(KIND) && rb->j[j].type == PK_JOINT_PRISMATIC) pn += q[j] * on[2];   // joint_slide
 #pragma unroll
         for (int u = 0; u < 3; ++u) o[u] = on[u];
@@ -215,7 +218,7 @@ PK_DEV bool eval_point(const RobotC *__restrict__ rb, const SolveParams &P, cons
         Q.ex[j * G::JW + 3 + Q.row] = p;
     }
     float Re[3], pe;
-    ee_frame_row(o, p, Q.fr[L], Q.fr[L] + 9, Re, pe);
+    ee_frame_row(o, p, Q.fr[L - 1], Q.fr[L - 1] + 9, Re, pe);
     // residual rows
     const float dr = pe - Q.tp;
     const float d[3] = {from<0>(dr), from<1>(dr), from<2>(dr)};
@@ -425,12 +428,15 @@ PK_DEV void quad_problem(const RobotC *__restrict__ rb, const float *__restrict_
         Q.pris[s] = pris_of(KIND) && rb->j[j].type == PK_JOINT_PRISMATIC;
     }
 #pragma unroll
-    for (int j = 0; j <= L; ++j)
+    for (int u = 0; u < 3; ++u) Q.g0[u] = rb->j[0].G[3 * Q.row + u];
+    Q.t0 = rb->j[0].t[Q.row];
+#pragma unroll
+    for (int j = 1; j <= L; ++j)
 #pragma unroll
         for (int u = 0; u < 12; ++u) {
-            Q.fr[j][u] = j < L ? (u < 9 ? rb->j[j].G[u] : rb->j[j].t[u - 9])
-                               : (u < 9 ? rb->e[0].G[u] : rb->e[0].t[u - 9]);
-            asm("" : "+v"(Q.fr[j][u]));     // in vector registers over the whole solve
+            Q.fr[j - 1][u] = j < L ? (u < 9 ? rb->j[j].G[u] : rb->j[j].t[u - 9])
+                                   : (u < 9 ? rb->e[0].G[u] : rb->e[0].t[u - 9]);
+            asm("" : "+v"(Q.fr[j - 1][u]));     // in vector registers over the whole solve
         }
     exchange();
     Q.tp = S[Q.row];

@@ -32,6 +32,14 @@ PK_DEV float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 PK_DEV float rsqrt_t(float d) { return __builtin_amdgcn_rsqf(d); }
 PK_DEV double rsqrt_t(double d) { return 1.0 / sqrt(d); }
 
+// A row (m0, m1, m2) of a joint's frame before its rotation, turned by Rz(q).
+PK_DEV void joint_turn_row(float m0, float m1, float m2, float s, float c, float *On)
+{
+    On[0] = m0 * c + m1 * s;
+    On[1] = m1 * c - m0 * s;
+    On[2] = m2;
+}
+
 // One row of joint_step: the parent frame's row (o, pp) -> the row of
 // p = pp + Op t and O = Op G Rz(q) with (s, c) = (sin q, cos q).
 PK_DEV void joint_step_row(const float *o, float pp, const float *G, const float *t, float s, float c,
@@ -41,9 +49,7 @@ PK_DEV void joint_step_row(const float *o, float pp, const float *G, const float
     float m0 = o[0] * G[0] + o[1] * G[3] + o[2] * G[6];
     float m1 = o[0] * G[1] + o[1] * G[4] + o[2] * G[7];
     float m2 = o[0] * G[2] + o[1] * G[5] + o[2] * G[8];
-    On[0] = m0 * c + m1 * s;
-    On[1] = m1 * c - m0 * s;
-    On[2] = m2;
+    joint_turn_row(m0, m1, m2, s, c, On);
 }
 
 // p = pp + Op t;  O = Op G Rz(q) with (s, c) = (sin q, cos q).
