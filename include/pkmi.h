@@ -282,15 +282,20 @@ typedef struct {
 
 typedef struct {
     int32_t iters_per_launch;    /* k; 0 = all iterations in one launch        */
-    int32_t waves_per_cu;        /* persistent grid = waves_per_cu x CUs wavefronts */
+    int32_t waves_per_cu;        /* persistent grid = waves_per_cu x CUs wavefronts
+                                    (twice that for the path-pair tree kernels,
+                                    which take half the registers)               */
     int32_t use_graph;           /* 1 = capture / replay a hipGraph             */
     int32_t workgroup_size;      /* threads per workgroup: 64, 128 or 256 (each
                                     wavefront pops its own work items); 0 = 64  */
-    int32_t mode;                /* PK_SCHED_SINGLE: every group in ONE persistent
-                                    launch per round, its wavefronts popping
-                                    (group, problem range) items from one device
-                                    queue (at most 8 groups; robots with at most 16
-                                    tree levels and 4 EEs); PK_SCHED_PER_GROUP: each
+    int32_t mode;                /* PK_SCHED_SINGLE: the groups in one chain of
+                                    persistent launches, a launch per round for all
+                                    groups of one kernel (path-pair trees of up to
+                                    8, 13 or 16 levels; every other path), its
+                                    wavefronts popping (group, problem range) items
+                                    from its device queue (at most 8 groups; robots
+                                    with at most 16 tree levels and 4 EEs);
+                                    PK_SCHED_PER_GROUP: each
                                     group's persistent launches on a stream of its
                                     own, the groups running concurrently         */
     int32_t variant[PK_MAX_GROUPS];  /* per group: lanes per problem, PK_VARIANT_LANE (1)

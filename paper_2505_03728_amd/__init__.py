@@ -482,8 +482,8 @@ class Context:
                        use_graph=True, variants=None, workgroup_size=0, mode=None):
         """groups: list of dicts rid, targets [tf, T], seeds [n, T*K], K, weights, out
         (from alloc_outputs).  variants: per group VARIANT_LANE / VARIANT_WAVE (None =
-        the options' choice).  mode: SCHED_SINGLE (one persistent launch per round over
-        every group, the default) or SCHED_PER_GROUP.  Zero k and waves_per_cu pick the
+        the options' choice).  mode: SCHED_SINGLE (persistent launches per round, one for
+        all groups of a kernel, the default) or SCHED_PER_GROUP.  Zero k and waves_per_cu pick the
         autotuned entry."""
         arr = self._groups_c(groups)
         v = (C.c_int32 * MAX_GROUPS)(*(list(variants or []) + [0] * MAX_GROUPS)[:MAX_GROUPS])

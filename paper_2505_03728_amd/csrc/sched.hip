@@ -1,12 +1,12 @@
 // Mixed-robot scheduler: several groups of IK problems (different robots,
-// shapes and device paths) solved in ONE persistent launch per round.
+// shapes and device paths) solved in rounds of a few persistent launches.
 //
 //  * A round runs every unfinished problem of every group for at most k more
 //    LM iterations.  A plan kernel turns the groups' active-list sizes into
 //    work items (64 problems for a per-lane path, one for a per-wavefront
-//    path), the persistent kernel's wavefronts pop items from one device
-//    queue and branch to the item's device path (lm_mixed.hip), and a
-//    compaction kernel packs the problems still unfinished into the next
+//    path), the wavefronts of one persistent launch per kernel pop items from
+//    its device queue and branch to the item's device path (lm_mixed.hip), and
+//    a compaction kernel packs the problems still unfinished into the next
 //    round's active lists, so problems that exited early stop taking lanes.
 //  * Problem state stays in HBM between rounds (resumable kernels).
 //  * The chain of rounds plus the per-group best-of-K is captured once into a
@@ -52,7 +52,7 @@ struct GroupPlan {
 struct TableEntry {
     std::string key;                 // buffers, weights, options, paths
     MixedArgs base;                  // the batch for the single launch (per-round fields unset)
-    int32_t *dev = nullptr;          // item_end [PK_MIX_GROUPS], then the queue head
+    int32_t *dev = nullptr;          // item_end [PK_MIX_GROUPS], then the queue heads
     int lds_floats = 0;              // per wavefront, largest over the batch's paths
     int max_n = 0;
     bool single_ok = false;          // every group has a path in the single launch
@@ -143,7 +143,10 @@ int path_of(const RobotC &H, int variant)
         return MIX_WAVE_64_8;
     }
     if (H.max_depth + 1 > 16 || H.m > 4) return MIX_WAVE_64_8;
-    if (variant == PK_VARIANT_WAVE && path_variant_available(H)) return MIX_PATH_16_4;
+    if (variant == PK_VARIANT_WAVE && path_variant_available(H)) {
+        const int levels = H.max_depth + 1;
+        return levels <= 8 ? MIX_PATH_8_4 : levels <= 13 ? MIX_PATH_13_4 : MIX_PATH_16_4;
+    }
     return MIX_WAVE_16_4;
 }
 
@@ -255,9 +258,9 @@ std::string data_key(int n_groups, const pk_ik_group *groups, const pk_lm_option
     return key + kb;
 }
 
-// The batch's single-launch description (built once per key) and its small
-// device buffers.  Wave paths go first in the queue: their items are the
-// longest.
+// The batch's description for the persistent launches (built once per key) and
+// its small device buffers.  Groups are in the order of their launches; in the
+// last one the wavefront path comes first: its items are longer than the lanes'.
 int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vector<GroupPlan> &plans,
               TableEntry **out)
 {
@@ -274,10 +277,10 @@ int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vec
     if (te.single_ok) {
         te.base.n_groups = (int)plans.size();
         int slot = 0;
-        for (int pass = 0; pass < 2; ++pass)
+        for (int pass = 0; pass <= PK_MIX_LAUNCHES; ++pass)
             for (const GroupPlan &pl : plans) {
-                const bool wave = pl.path == MIX_WAVE_16_4 || pl.path == MIX_PATH_16_4;
-                if (wave != (pass == 0)) continue;
+                const bool wave = pl.path != MIX_LANE_ARM && pl.path != MIX_LANE_HAND;
+                if (pass != mixed_launch_of(pl.path) + (wave ? 0 : 1)) continue;
                 MixedGroup &G = te.base.g[slot++];
                 G.rb = pl.rb->dev;
                 G.qr = pl.P.q_rest ? pl.P.q_rest : pl.rb->dev->mid;
@@ -319,15 +322,15 @@ void rounds_of(int max_it, int k, int &kk, int &rounds)
     rounds = max_it > 0 ? (max_it + kk - 1) / kk : 1;
 }
 
-// Single mode: the whole chain on one stream, rounds of (plan, one
-// persistent launch over every group, compaction), then best-of-K per
+// Single mode: the whole chain on one stream, rounds of (plan, persistent
+// launches over the groups of each kernel, compaction), then best-of-K per
 // group.  Valid eagerly and under capture.
 hipError_t enqueue_single(pk_ctx *ctx, const TableEntry &te, std::vector<GroupPlan> &plans, int k,
                           int wpc, int wg, hipStream_t s)
 {
     int kk, rounds;
     rounds_of(plans[0].P.max_iters, k, kk, rounds);
-    const int waves = wpc * cu_count(ctx);
+    const int cus = cu_count(ctx);
     for (int r = 0; r < rounds; ++r) {
         MixedArgs a = te.base;
         a.round = r;
@@ -340,7 +343,7 @@ hipError_t enqueue_single(pk_ctx *ctx, const TableEntry &te, std::vector<GroupPl
             G.P.n_active = r > 0 ? G.count + cur : nullptr;
         }
         hipError_t e = launch_mixed_round(a, te.dev, te.dev + PK_MIX_GROUPS, te.max_n, r + 1 == rounds,
-                                          waves, wg, te.lds_floats, s);
+                                          wpc, cus, wg, s);
         if (e != hipSuccess) return e;
     }
     for (GroupPlan &pl : plans)
