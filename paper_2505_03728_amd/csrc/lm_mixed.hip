@@ -194,22 +194,25 @@ hipError_t launch_groups(const MixedArgs &a, int &g0, int32_t *item_end, int32_t
 }
 
 // Whether one launch serves the whole round: the batch has more than one kernel
-// and a kernel with every path holds all its items at once.  Then no item waits
-// for another and the round takes as long as its slowest; split, the launches'
-// times add up.  Past that the trees' wavefronts queue behind each other.
+// and the kernel with every path holds all its trees at once (they are first in
+// the queue).  Then they run beside the other items; split, the launches' times
+// add up.  Past that they queue behind each other there.  60000 arms and 20000
+// hands (50 iterations; 1536 wavefronts held) in us: with 400 trees 679 in one
+// launch and 1121 split, with 1000 trees 949 and 1171; with 2000 trees 1260 split
+// (1329 in one launch of the kernel that this one replaces).
 bool one_launch(const MixedArgs &a, int wpc, int cus, int wg)
 {
-    int64_t items = 0;
+    int64_t trees = 0;
     int ldsf = 0;
     bool same = true;
     for (int g = 0; g < a.n_groups; ++g) {
-        items += (a.g[g].P.N + a.g[g].per_item - 1) / a.g[g].per_item;
+        if (mixed_launch_of(a.g[g].path) < PK_MIX_LAUNCHES - 1) trees += a.g[g].P.N;
         ldsf = std::max(ldsf, mixed_lds_floats(a.g[g].path));
         same = same && mixed_launch_of(a.g[g].path) == mixed_launch_of(a.g[0].path);
     }
     const int wpb = wg / 64, block_lds = wpb * ldsf * (int)sizeof(float);
-    const int held = std::min(8, wpb * (160 * 1024 / block_lds));   // per CU (253 VGPRs: 2 per SIMD)
-    return !same && items <= (int64_t)std::min(wpc, held) * cus;
+    const int held = std::min(8, wpb * (160 * 1024 / block_lds));   // per CU (237 VGPRs: 2 per SIMD)
+    return !same && trees <= (int64_t)std::min(wpc, held) * cus;
 }
 
 hipError_t launch_mixed_round(const MixedArgs &a, int32_t *item_end, int32_t *heads, int max_n,

@@ -15,7 +15,7 @@ DEV = "cuda:0"
 AXES = "zyzyzyzyzyzyzyzy"
 
 
-# (64: past the items that one launch holds)
+# (64: past the trees that one launch holds)
 @pytest.mark.parametrize("scale", [1, 64])
 @pytest.mark.parametrize("k,wg", [(0, 64), (4, 64), (0, 128), (5, 256)])
 def test_mixed_levels_equal_separate(k, wg, scale):
