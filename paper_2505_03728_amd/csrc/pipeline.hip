@@ -4,6 +4,7 @@
 // problems are compacted into an active list that a persistent LM launch
 // (wavefronts popping items from a device queue) reads, so the host never
 // synchronises and a pass costs what its listed problems cost.
+#include <limits.h>
 #include <string.h>
 
 #include <algorithm>
@@ -20,46 +21,94 @@ __global__ void fill_i32_kernel(int64_t count, int32_t v, int32_t *p)
     if (i < count) p[i] = v;
 }
 
+// Threads of a block whose targets are to be listed take consecutive places:
+// one atomic per counter and block (with one per target the counter's line
+// served 30000 of them one after the other: 131072 targets, lists of 29634 and
+// 12080, 49 and 78 us; 6.6 and 7.9 now).  per: problems a target lists.
+// Returns the place of this thread's target in units of targets.
+constexpr int LIST_BLOCK = 1024;
+
+PK_DEV int list_places(bool need, int per, int32_t *count_t, int32_t *count_p, int32_t *count_stage)
+{
+    __shared__ int wave_n[LIST_BLOCK / 64], base;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint64_t mask = __ballot(need);
+    if (lane == 0) wave_n[w] = __popcll(mask);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int u = 0; u < LIST_BLOCK / 64; ++u) {
+            const int c = wave_n[u];
+            wave_n[u] = sum;
+            sum += c;
+        }
+        base = 0;
+        if (sum) {
+            // the list's own counter gives the place; the others only count
+            const int at = atomicAdd(count_stage ? count_stage : count_p, sum * per);
+            base = at / per;
+            if (count_stage) atomicAdd(count_p, sum * per);
+            if (count_t) atomicAdd(count_t, sum);
+        }
+    }
+    __syncthreads();
+    return base + wave_n[w] + __popcll(mask & ((1ull << lane) - 1));
+}
+
+// The listed targets' problems t * Kf + c0 + k, k < per, at place * per of the
+// list; the wavefront writes them for one of its targets after the other.
+PK_DEV void list_write(bool need, int64_t t, int place, int Kf, int c0, int per, int32_t *active)
+{
+    const int lane = threadIdx.x & 63;
+    for (uint64_t mask = __ballot(need); mask; mask &= mask - 1) {
+        const int src = __builtin_ctzll(mask);
+        const int64_t tt = __shfl(t, src, 64), at = (int64_t)__shfl(place, src, 64) * per;
+        for (int k = lane; k < per; k += 64) active[at + k] = (int32_t)(tt * Kf + c0 + k);
+    }
+}
+
 // Targets not solved (success[t] == 0) -> active problem list of a later
 // pass (Kf problems per target, problem t * Kf + k).
-__global__ void fallback_list_kernel(int64_t T, int Kf, const int32_t *__restrict__ success,
-                                     int32_t *count_t, int32_t *count_p, int32_t *active)
+__global__ __launch_bounds__(LIST_BLOCK) void fallback_list_kernel(int64_t T, int Kf,
+                                                                   const int32_t *__restrict__ success,
+                                                                   int32_t *count_t, int32_t *count_p,
+                                                                   int32_t *active)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T || success[t]) return;
-    const int pos = atomicAdd(count_t, 1);
-    atomicAdd(count_p, Kf);
-    for (int k = 0; k < Kf; ++k) active[(int64_t)pos * Kf + k] = (int32_t)(t * Kf + k);
+    const int64_t t = (int64_t)blockIdx.x * LIST_BLOCK + threadIdx.x;
+    const bool need = t < T && !success[t];
+    list_write(need, t, list_places(need, Kf, count_t, count_p, nullptr), Kf, 0, Kf, active);
 }
 
 // Fallback stage [c0, c1) of every target's Kf random seeds.  Stage 0 lists
 // the targets the earlier passes left unsolved; a later stage lists those
 // that ran the previous stage [cp, c0) and got no converged problem from it.
 // done[t] counts the target's fallback seeds run so far.
-__global__ void fallback_stage_kernel(int64_t T, int Kf, int cp, int c0, int c1,
-                                      const int32_t *__restrict__ success,
-                                      const int32_t *__restrict__ status, int32_t *done,
-                                      int32_t *count_t, int32_t *count_p, int32_t *count_stage,
-                                      int32_t *active)
+__global__ __launch_bounds__(LIST_BLOCK) void fallback_stage_kernel(
+    int64_t T, int Kf, int cp, int c0, int c1, const int32_t *__restrict__ success,
+    const int32_t *__restrict__ status, int32_t *done, int32_t *count_t, int32_t *count_p,
+    int32_t *count_stage, int32_t *active)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
+    const int64_t t = (int64_t)blockIdx.x * LIST_BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    bool need = t < T;
     if (c0 == 0) {
-        if (success[t]) {
+        if (need && success[t]) {
             done[t] = 0;
-            return;
+            need = false;
         }
     } else {
-        if (done[t] != c0) return;
-        for (int k = cp; k < c0; ++k)
-            if ((status[t * Kf + k] & 0xff) == PK_CONVERGED) return;
+        need = need && done[t] == c0;
+        for (uint64_t mask = __ballot(need); mask; mask &= mask - 1) {
+            const int src = __builtin_ctzll(mask);
+            const int64_t tt = __shfl(t, src, 64);
+            bool conv = false;
+            for (int k = cp + lane; k < c0; k += 64) conv |= (status[tt * Kf + k] & 0xff) == PK_CONVERGED;
+            if (__ballot(conv) && lane == src) need = false;
+        }
     }
-    done[t] = c1;
+    if (need) done[t] = c1;
     const int w = c1 - c0;
-    const int pos = atomicAdd(count_stage, w);
-    if (count_t) atomicAdd(count_t, 1);
-    atomicAdd(count_p, w);
-    for (int k = 0; k < w; ++k) active[pos + k] = (int32_t)(t * Kf + c0 + k);
+    list_write(need, t, list_places(need, w, count_t, count_p, count_stage), Kf, c0, w, active);
 }
 
 struct MergeArgs {
@@ -73,42 +122,110 @@ struct MergeArgs {
     int32_t *success, *source, *itt;
 };
 
-__global__ void merge_kernel(MergeArgs a)
+// A number whose order is the float's by `<` (-0 made +0, equal to it), a NaN
+// after every number; with the index below it the least is the first smallest.
+PK_DEV uint64_t pick_key(float v, int k)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.T) return;
+    const uint32_t u = __float_as_uint(v + 0.f);
+    const uint32_t o = v != v ? 0xffffffffu : u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+    return (uint64_t)o << 32 | (uint32_t)k;
+}
+
+PK_DEV uint64_t wave_min(uint64_t v)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+        const uint64_t o = __shfl_xor((unsigned long long)v, d, 64);
+        v = o < v ? o : v;
+    }
+    return v;
+}
+
+// best_of_k_pick by a whole wavefront, K >= 1.  (Its comparisons are `<` from
+// the first candidate on, so a NaN wins exactly where it is that first one.)
+PK_DEV int wave_best_of_k(const int32_t *status, const float *cost, const float *pcost, int64_t base, int K,
+                          bool &any)
+{
+    uint64_t bc = ~0ull, bp = ~0ull, first = ~0ull;
+    for (int k = threadIdx.x & 63; k < K; k += 64) {
+        const int32_t st = status[base + k];
+        const float c = cost[base + k], pc = pcost[base + k];
+        if ((st & 0xff) == PK_CONVERGED) {
+            const uint64_t key = pick_key(c, k);
+            bc = key < bc ? key : bc;
+            // the first candidate's index, then whether it is a NaN
+            const uint64_t f = (uint64_t)k << 1 | (c != c ? 1 : 0);
+            first = f < first ? f : first;
+        }
+        const uint64_t key = pick_key(pc, k);
+        bp = key < bp ? key : bp;
+        if (k == 0 && pc != pc) bp = 0;   // (lane 0, its first candidate: stays the least)
+    }
+    first = wave_min(first);
+    any = first != ~0ull;
+    if (any) return first & 1 ? (int)(first >> 1) : (int)(uint32_t)wave_min(bc);
+    return (int)(uint32_t)wave_min(bp);
+}
+
+// Eight lanes per target: its iterations to tolerance and its joints are a
+// read each of consecutive values.  The fallback's targets take the whole
+// wavefront, one after the other.  131072 targets of 8 seeds, 12080 of them in a
+// fallback of 128: 103 us with a thread per target (chains of dependent reads
+// 32 bytes and more apart), 33 now.
+constexpr int MERGE_LANES = 8, MERGE_BLOCK = 256;
+
+__global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(MergeArgs a)
+{
+    const int64_t t = ((int64_t)blockIdx.x * MERGE_BLOCK + threadIdx.x) / MERGE_LANES;
+    const int lane = threadIdx.x & 63, sub = lane % MERGE_LANES;
     const int64_t NA = a.T * a.K, NB = a.T * a.Kf;
-    int src = -1, it = -1;
+    const bool live = t < a.T;
     // pass A (learned seeds), or its restart: best_a / itt_a then hold the
     // restart's values for the targets that were restarted
-    const bool restarted = a.succ_r && !a.succ_a[t];
-    if (a.succ_a[t] || (restarted && a.succ_r[t])) {
-        src = restarted ? 2 : 0;
+    const bool sa = live && a.succ_a[t] != 0;
+    const bool restarted = live && a.succ_r && !sa;
+    const bool solved = sa || (restarted && a.succ_r[t] != 0);
+    const bool fallback = live && !solved && a.Kf > 0;
+    int src = solved ? (restarted ? 2 : 0) : -1, it = INT_MAX;
+    if (live && !fallback) {
         const int b = a.best_a[t];
-        for (int j = 0; j < a.n; ++j) a.best_joints[(int64_t)j * a.T + t] = a.joints_a[(int64_t)j * NA + t * a.K + b];
-        for (int k = 0; k < a.K; ++k) {
-            const int v = a.itt_a[t * a.K + k];
-            if (v >= 0 && (it < 0 || v < it)) it = v;
-        }
-        if (restarted) it += a.refine_its;
-    } else if (a.Kf > 0) {
+        for (int j = sub; j < a.n; j += MERGE_LANES)
+            a.best_joints[(int64_t)j * a.T + t] = a.joints_a[(int64_t)j * NA + t * a.K + b];
+        if (solved)
+            for (int k = sub; k < a.K; k += MERGE_LANES) {
+                const int v = a.itt_a[t * a.K + k];
+                it = v >= 0 && v < it ? v : it;
+            }
+    }
+#pragma unroll
+    for (int d = 1; d < MERGE_LANES; d *= 2) it = min(it, __shfl_xor(it, d, 64));
+    it = it == INT_MAX ? -1 : it;
+    if (solved && restarted) it += a.refine_its;
+    for (uint64_t mask = __ballot(fallback && sub == 0); mask; mask &= mask - 1) {
         // the fallback seeds this target ran (every stage up to its first
         // converged problem)
-        const int kr = a.done_b[t];
+        const int from = __builtin_ctzll(mask);
+        const int64_t tt = __shfl(t, from, 64);
+        const int kr = a.done_b[tt];
         bool any;
-        const int b = best_of_k_pick(a.status_b, a.cost_b, a.pcost_b, t * a.Kf, kr, any);
-        for (int j = 0; j < a.n; ++j) a.best_joints[(int64_t)j * a.T + t] = a.joints_b[(int64_t)j * NB + t * a.Kf + b];
+        const int b = wave_best_of_k(a.status_b, a.cost_b, a.pcost_b, tt * a.Kf, kr, any);
+        for (int j = lane; j < a.n; j += 64)
+            a.best_joints[(int64_t)j * a.T + tt] = a.joints_b[(int64_t)j * NB + tt * a.Kf + b];
         if (any) {
-            src = 1;
-            for (int k = 0; k < kr; ++k) {
-                const int v = a.itt_b[t * a.Kf + k];
-                if (v >= 0 && (it < 0 || v < it)) it = v;
+            int v = INT_MAX;
+            for (int k = lane; k < kr; k += 64) {
+                const int u = a.itt_b[tt * a.Kf + k];
+                v = u >= 0 && u < v ? u : v;
+            }
+#pragma unroll
+            for (int d = 1; d < 64; d *= 2) v = min(v, __shfl_xor(v, d, 64));
+            if (lane == from) {
+                src = 1;
+                it = v == INT_MAX ? -1 : v;
             }
         }
-    } else {
-        const int b = a.best_a[t];
-        for (int j = 0; j < a.n; ++j) a.best_joints[(int64_t)j * a.T + t] = a.joints_a[(int64_t)j * NA + t * a.K + b];
     }
+    if (!live || sub != 0) return;
     if (a.success) a.success[t] = src >= 0 ? 1 : 0;
     if (a.source) a.source[t] = src;
     if (a.itt) a.itt[t] = it;
@@ -248,7 +365,7 @@ extern "C" int pk_ik_solve_seeded(pk_ctx *ctx, int32_t robot_id, int64_t T, cons
             hipLaunchKernelGGL(fill_i32_kernel, dim3(nblk(NA, 256)), dim3(256), 0, s, NA, 0, out->restart_iters);
         if (out->restart_accepts)
             hipLaunchKernelGGL(fill_i32_kernel, dim3(nblk(NA, 256)), dim3(256), 0, s, NA, 0, out->restart_accepts);
-        hipLaunchKernelGGL(fallback_list_kernel, dim3(nblk(T, 256)), dim3(256), 0, s, T, K, succ_a,
+        hipLaunchKernelGGL(fallback_list_kernel, dim3(nblk(T, LIST_BLOCK)), dim3(LIST_BLOCK), 0, s, T, K, succ_a,
                            counters + 2, counters + 3, list_r);
         SolveParams PR = PA;
         PR.max_iters = R;
@@ -279,7 +396,7 @@ extern "C" int pk_ik_solve_seeded(pk_ctx *ctx, int32_t robot_id, int64_t T, cons
         for (int cp = 0, c0 = 0; c0 < Kf; cp = c0, c0 += Kc) {
             const int c1 = std::min(Kf, c0 + Kc);
             hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, (int64_t)2, 0, counters + 4);
-            hipLaunchKernelGGL(fallback_stage_kernel, dim3(nblk(T, 256)), dim3(256), 0, s, T, Kf, cp, c0,
+            hipLaunchKernelGGL(fallback_stage_kernel, dim3(nblk(T, LIST_BLOCK)), dim3(LIST_BLOCK), 0, s, T, Kf, cp, c0,
                                c1, succ_now, status_b, done_b, c0 == 0 ? counters : nullptr, counters + 1,
                                counters + 5, active);
             PK_HIP(ctx, hipGetLastError());
@@ -293,7 +410,7 @@ extern "C" int pk_ik_solve_seeded(pk_ctx *ctx, int32_t robot_id, int64_t T, cons
     m.status_b = status_b; m.itt_b = itt_b; m.done_b = done_b; m.cost_b = cost_b; m.pcost_b = pcost_b; m.joints_b = joints_b;
     m.best_joints = out->best_joints; m.success = out->target_success; m.source = out->source;
     m.itt = out->iters_to_tol;
-    hipLaunchKernelGGL(merge_kernel, dim3(nblk(T, 256)), dim3(256), 0, s, m);
+    hipLaunchKernelGGL(merge_kernel, dim3(nblk(T * MERGE_LANES, MERGE_BLOCK)), dim3(MERGE_BLOCK), 0, s, m);
     PK_HIP(ctx, hipGetLastError());
     if (out->n_fallback)
         PK_HIP(ctx, hipMemcpyAsync(out->n_fallback, counters, 4, hipMemcpyDeviceToDevice, s));
