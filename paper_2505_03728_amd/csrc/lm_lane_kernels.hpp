@@ -13,6 +13,10 @@ namespace quad {
 template <int L, int KIND>
 hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const BestOut *best);
 }
+namespace star {
+inline hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blocks, hipStream_t s,
+                         const BestOut *best);
+}
 
 namespace lane {
 
@@ -31,6 +35,15 @@ inline int64_t quad_max_problems(int chain_len) { return chain_len <= 8 ? 32768 
 inline bool takes_quad(int chains, int chain_len, const SolveParams &P)
 {
     return chains == 1 && !P.target_exit && P.N <= quad_max_problems(chain_len);
+}
+
+// The star of four chains of four joints with position EEs runs with four lanes
+// per problem, a chain each (lm_star.hpp: faster at every size measured, 64 to a
+// million problems); the per-lane kernel keeps target_exit, which is defined on
+// its runs of lanes.
+inline bool takes_star(int chains, int chain_len, const SolveParams &P)
+{
+    return chains == 4 && chain_len == 4 && !P.target_exit;
 }
 
 // Next work item of this block: the block index for a plain grid, else an
@@ -140,6 +153,9 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
         if (!persist && !P.active && !P.n_active && !P.st_state && takes_quad(C, L, P))
             return quad::launch<L, KIND>(rb, P, s, best);
     }
+    if constexpr (C == 4) {
+        if (takes_star(C, L, P)) return star::launch(rb, P, persist_blocks, s, best);
+    }
     if (persist && persist_blocks > 0 && persist_blocks < grid) grid = persist_blocks;
     // rest pose: caller's array, else the robot's mid-range table
     const float *qr = P.q_rest ? P.q_rest : rb->mid;
@@ -148,12 +164,14 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
     if (persist && P.target_exit)
         hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P);
-    else if (persist)
-        hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P);
     else if (P.target_exit)
         hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P, B);
-    else
-        hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P, B);
+    else if constexpr (C == 1) {
+        if (persist)
+            hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P);
+        else
+            hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P, B);
+    }
     return hipGetLastError();
 }
 
@@ -171,3 +189,4 @@ hipError_t launch_lane_chain_c(int L, int kind, const RobotC *rb, const SolvePar
 }  // namespace pk
 
 #include "lm_quad.hpp"
+#include "lm_star.hpp"

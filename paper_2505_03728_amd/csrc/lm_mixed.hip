@@ -1,30 +1,29 @@
 // Persistent LM launches over a mixed batch: the wavefronts of a grid pop work
 // items from a device queue; an item is (group, range of that group's active
-// problems): 64 problems for a per-lane path, one for a per-wavefront path.
+// problems): 64 problems for a per-lane path, 16 for the star's four lanes per
+// problem, one for a per-wavefront path.
 // The wavefront branches (uniformly) to the device path of the item's group,
 // which runs the problems for at most k more LM iterations with their state in
 // HBM (resumable), so a problem's result does not depend on k, on the grid or
 // on which wavefront takes it.
 //
 // A round of a large batch is up to four launches, one after the other: one per
-// row length of the path-pair kernel (one tree problem per wavefront), then one for all other
-// paths.  A kernel that holds every path takes the registers of the per-lane
-// arm (253: two wavefronts per SIMD) and the LDS of the per-lane hand (26 KiB:
-// six per CU), and the trees, which need four wavefronts per SIMD to cover
-// their LDS and dependency waits, run at 16 levels' row length.  60000 arms,
-// 20000 hands and 4096 trees of 34 joints, 50 iterations, in us: trees 1454 in
-// such a kernel; 1326 in one of their own (128 VGPRs, 9.4 KiB, two row lengths,
-// the LDS slice of unknown alignment: 32-bit accesses); 935 with the slice's
-// alignment and the robot in constant memory known; 833 at their own row
-// length.  The whole batch 2246, now 1390.  The groups of the last launch are
-// fewer wavefronts than the chip holds and overlap in it (572; 304 and 448
-// each by itself).
+// row length of the path-pair kernel (one tree problem per wavefront), then one
+// for all other paths.  A kernel that holds every path takes the registers of
+// the per-lane arm (253: two wavefronts per SIMD), and the trees, which need four
+// to cover their LDS and dependency waits, run at 16 levels' row length.  4096
+// trees of 34 joints, 50 iterations, in us: 1454 in such a kernel; 1326 in one of
+// their own (128 VGPRs, 9.4 KiB, two row lengths, the LDS slice of unknown
+// alignment: 32-bit accesses); 935 with the slice's alignment and the robot in
+// constant memory known; 833 at their own row length.  With 60000 arms and
+// 20000 hands the batch took 2246, 1390 with these launches, 1134 with the hands
+// on four lanes per problem (lm_star.hpp).
 //
 // Method: Sec. III-A (LM over the sum of squared weighted residuals) for each
 // problem, as in the per-lane and per-wavefront kernels it instantiates.
 #include <algorithm>
 
-#include "lm_lane.hpp"
+#include "lm_lane_kernels.hpp"
 #include "lm_path.hpp"
 #include "lm_wave.hpp"
 #include "sched_table.hpp"
@@ -86,6 +85,16 @@ PK_DEV void run_lane(const MixedGroup &G, float *ws, int64_t first, int lane)
     if (i < nact) lane::lane_problem<C, L, KIND, true>(constant(G.rb), constant(G.qr), P, lane::LaneLds{ws + lane}, i);
 }
 
+// Star path: problems first*16 + quad of the group's active list.
+PK_DEV void run_star(const MixedGroup &G, int64_t first, int lane)
+{
+    const SolveParams &P = G.P;
+    const int64_t nact = P.n_active ? (int64_t)*P.n_active : P.N;
+    const int64_t i = first * 16 + (lane >> 2);
+    star::Final fin;
+    if (i < nact) star::star_problem<true>(constant(G.rb), constant(G.qr), P, i, &fin);
+}
+
 // One tree problem on this wavefront.
 template <int DMAX, int RW>
 PK_DEV void run_path(const MixedGroup &G, int g, float *ws, int64_t first)
@@ -128,8 +137,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(LAUNCH < 3 ?
             case MIX_LANE_ARM:
                 run_lane<1, 7, PK_EE_POSE>(G, ws, first, lane);
                 break;
-            case MIX_LANE_HAND:
-                run_lane<4, 4, PK_EE_POSITION>(G, ws, first, lane);
+            case MIX_STAR_HAND:
+                run_star(G, first, lane);
                 break;
             case MIX_WAVE_16_4:
                 wave::wave_problem<16, 4>(constant(G.rb), G.P, ws, first);
@@ -152,7 +161,7 @@ int mixed_lds_floats(int path)
 {
     switch (path) {
     case MIX_LANE_ARM: return align4(lane::Slots<1, 7, PK_EE_POSE>::TOTAL * lane::BLOCK);
-    case MIX_LANE_HAND: return align4(lane::Slots<4, 4, PK_EE_POSITION>::TOTAL * lane::BLOCK);
+    case MIX_STAR_HAND: return 0;
     case MIX_WAVE_16_4: return align4(wave::Lds<16, 4>::FLOATS);
     case MIX_PATH_16_4:
     case MIX_PATH_13_4: return align4(path::Lds<16, 4>::FLOATS);
@@ -197,9 +206,9 @@ hipError_t launch_groups(const MixedArgs &a, int &g0, int32_t *item_end, int32_t
 // and the kernel with every path holds all its trees at once (they are first in
 // the queue).  Then they run beside the other items; split, the launches' times
 // add up.  Past that they queue behind each other there.  60000 arms and 20000
-// hands (50 iterations; 1536 wavefronts held) in us: with 400 trees 679 in one
-// launch and 1121 split, with 1000 trees 949 and 1171; with 2000 trees 1260 split
-// (1329 in one launch of the kernel that this one replaces).
+// hands with 400, 1000 and 2000 trees, 50 iterations, in us: 523, 607 and 810 in
+// one launch; with a line that split them (hands still one per lane): 1121, 1171
+// and 1260.
 bool one_launch(const MixedArgs &a, int wpc, int cus, int wg)
 {
     int64_t trees = 0;
@@ -210,7 +219,7 @@ bool one_launch(const MixedArgs &a, int wpc, int cus, int wg)
         ldsf = std::max(ldsf, mixed_lds_floats(a.g[g].path));
         same = same && mixed_launch_of(a.g[g].path) == mixed_launch_of(a.g[0].path);
     }
-    const int wpb = wg / 64, block_lds = wpb * ldsf * (int)sizeof(float);
+    const int wpb = wg / 64, block_lds = std::max(1, wpb * ldsf * (int)sizeof(float));
     const int held = std::min(8, wpb * (160 * 1024 / block_lds));   // per CU (237 VGPRs: 2 per SIMD)
     return !same && trees <= (int64_t)std::min(wpc, held) * cus;
 }

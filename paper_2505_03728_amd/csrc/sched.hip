@@ -3,8 +3,7 @@
 //
 //  * A round runs every unfinished problem of every group for at most k more
 //    LM iterations.  A plan kernel turns the groups' active-list sizes into
-//    work items (64 problems for a per-lane path, one for a per-wavefront
-//    path), the wavefronts of one persistent launch per kernel pop items from
+//    work items (a wavefront's problems on the group's device path), the wavefronts of one persistent launch per kernel pop items from
 //    its device queue and branch to the item's device path (lm_mixed.hip), and
 //    a compaction kernel packs the problems still unfinished into the next
 //    round's active lists, so problems that exited early stop taking lanes.
@@ -53,7 +52,7 @@ struct TableEntry {
     std::string key;                 // buffers, weights, options, paths
     MixedArgs base;                  // the batch for the single launch (per-round fields unset)
     int32_t *dev = nullptr;          // item_end [PK_MIX_GROUPS], then the queue heads
-    int lds_floats = 0;              // per wavefront, largest over the batch's paths
+    int lds_floats = 0;              // mixed_lds_limit, largest over the batch's paths
     int max_n = 0;
     bool single_ok = false;          // every group has a path in the single launch
 };
@@ -139,7 +138,7 @@ int path_of(const RobotC &H, int variant)
 {
     if (variant == PK_VARIANT_LANE) {
         if (H.chains == 1 && H.chain_len == 7 && H.e[0].kind == PK_EE_POSE) return MIX_LANE_ARM;
-        if (H.chains == 4 && H.chain_len == 4 && H.e[0].kind == PK_EE_POSITION) return MIX_LANE_HAND;
+        if (H.chains == 4 && H.chain_len == 4 && H.e[0].kind == PK_EE_POSITION) return MIX_STAR_HAND;
         return MIX_WAVE_64_8;
     }
     if (H.max_depth + 1 > 16 || H.m > 4) return MIX_WAVE_64_8;
@@ -279,7 +278,7 @@ int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vec
         int slot = 0;
         for (int pass = 0; pass <= PK_MIX_LAUNCHES; ++pass)
             for (const GroupPlan &pl : plans) {
-                const bool wave = pl.path != MIX_LANE_ARM && pl.path != MIX_LANE_HAND;
+                const bool wave = pl.path != MIX_LANE_ARM && pl.path != MIX_STAR_HAND;
                 if (pass != mixed_launch_of(pl.path) + (wave ? 0 : 1)) continue;
                 MixedGroup &G = te.base.g[slot++];
                 G.rb = pl.rb->dev;
@@ -290,8 +289,8 @@ int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vec
                 G.list[1] = pl.lists[1];
                 G.count = pl.counters;
                 G.path = pl.path;
-                G.per_item = wave ? 1 : 64;
-                te.lds_floats = std::max(te.lds_floats, mixed_lds_floats(pl.path));
+                G.per_item = wave ? 1 : pl.path == MIX_STAR_HAND ? 16 : 64;
+                te.lds_floats = std::max(te.lds_floats, mixed_lds_limit(pl.path));
                 te.max_n = std::max(te.max_n, (int)pl.P.N);
             }
         if (hipMalloc(&te.dev, 256) != hipSuccess)
@@ -719,7 +718,7 @@ int pk_autotune_mixed(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
             const int path = path_of(robot_of(ctx, groups[g].robot_id)->host,
                                      vs[g] == PK_VARIANT_WAVE ? PK_VARIANT_WAVE : PK_VARIANT_LANE);
             single = single && path != MIX_WAVE_64_8;
-            if (path != MIX_WAVE_64_8) ldsf = std::max(ldsf, mixed_lds_floats(path));
+            if (path != MIX_WAVE_64_8) ldsf = std::max(ldsf, mixed_lds_limit(path));
         }
         for (int mode : {PK_SCHED_SINGLE, PK_SCHED_PER_GROUP})
         for (int k : ks)

@@ -19,7 +19,7 @@ namespace pk {
 // class) instantiation).
 enum MixedPath : int32_t {
     MIX_LANE_ARM = 0,     // one problem per lane, serial 7-joint arm, one pose EE
-    MIX_LANE_HAND = 1,    // one problem per lane, 4 chains of 4 joints, 4 position EEs
+    MIX_STAR_HAND = 1,    // four lanes per problem, 4 chains of 4 joints, 4 position EEs
     MIX_WAVE_16_4 = 2,    // one problem per wavefront, lane per joint, depth <= 16 levels, <= 4 EEs
     MIX_PATH_16_4 = 3,    // one problem per wavefront, lane per (joint, EE path) pair,
                           // depth <= 16 levels, <= 4 EEs
@@ -52,7 +52,7 @@ struct MixedGroup {
     int32_t *list[2];         // active lists of alternate rounds
     int32_t *count;           // [2] active-list sizes
     int32_t path;             // MixedPath
-    int32_t per_item;         // problems per work item: 64 (lane paths) or 1 (wavefront paths)
+    int32_t per_item;         // problems per work item: 64 (lane), 16 (star) or 1 (wavefront paths)
 };
 
 struct MixedArgs {
@@ -63,6 +63,14 @@ struct MixedArgs {
 
 // LDS floats one wavefront needs on a path.
 int mixed_lds_floats(int path);
+
+// LDS floats per wavefront that decide which workgroup sizes a batch is served
+// with.  The star uses none, but its groups keep the sizes of the per-lane
+// kernel that served them before it (104 slots of 64 lanes).
+inline int mixed_lds_limit(int path)
+{
+    return path == MIX_STAR_HAND ? 104 * 64 : mixed_lds_floats(path);
+}
 
 // Enqueues one round on stream s: plan (work items per group into item_end,
 // queue heads reset), persistent solves (each problem at most P.iter_budget
