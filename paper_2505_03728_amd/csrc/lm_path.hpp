@@ -365,9 +365,7 @@ PK_DEV T jtj_rows(const float *lds, const LaneInfo<DMAX> &I, int lane, int max_d
                   Row<T, RW> &r, T &g)
 {
     using L = Lds<DMAX, MMAX>;
-    // new values (as in path_solve): the per-depth conditions are formed here
-    int dep = I.dep;
-    __asm__ volatile("" : "+v"(dep));
+    // a new value (as in path_solve): the per-depth conditions are formed here
     max_depth = fresh_uniform(max_depth);
     const float *own = lds + L::JC + lane * 8;
     float cj[6];
@@ -379,19 +377,21 @@ PK_DEV T jtj_rows(const float *lds, const LaneInfo<DMAX> &I, int lane, int max_d
 #pragma unroll
         for (int u = 0; u < 6; ++u) g += (T)cj[u] * (T)rs[u];
     }
+    // (a lane is its own ancestor at its depth; lanes without a joint hold zeros)
     T diag = 0;
 #pragma unroll
-    for (int d = 0; d < DMAX; ++d) {
+    for (int u = 0; u < 6; ++u) diag += (T)cj[u] * (T)cj[u];
+#pragma unroll
+    for (int d = 0; d < RW; ++d) {
         T s = 0;
-        if (d <= max_depth) {
+        if (d < max_depth) {
             const float *ca = lds + L::JC + wave::anc_lane<DMAX>(I.ancp, d) * 8;
 #pragma unroll
             for (int u = 0; u < 6; ++u) s += (T)cj[u] * (T)ca[u];
         }
         // entries at and past the lane's depth take values no reader uses
-        if (d < RW) r.set(d < RW ? d : 0, s);
-        diag = d == dep ? s : diag;
-        __asm__ volatile("" ::: "memory");   // one ancestor block in flight at a time
+        r.set(d, s);
+        if (d & 1) __asm__ volatile("" ::: "memory");   // two ancestor blocks in flight at a time
     }
     return diag;
 }
