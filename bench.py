@@ -836,7 +836,7 @@ def run_mobile(args):
                 fp64_fallback_fraction=float(((st & 0x100) != 0).mean()),
                 roofline={"bound": "alu", "achieved": round(ach, 4), "peak": FP32_VALU_PEAK,
                           "unit": "TFLOP/s", "frac": round(ach / FP32_VALU_PEAK, 6), "traffic": None,
-                          "kernel": (f"lm_lane_kernel<1,{ctx.robot_info(rid)['chain_len']},pose+prismatic>"
+                          "kernel": (f"lm_quad_kernel<{ctx.robot_info(rid)['chain_len']},pose+prismatic>"
                                      if ctx.robot_info(rid)["chains"] == 1 else "lm_path_kernel<16,4>"),
                           "kernel_ms": round(ms, 5), "algorithmic_flops": flops})
     if not args.no_cpu:
