@@ -12,7 +12,7 @@
 // Bound: the layer-by-layer step was 26 launches that moved every activation
 // several times and read the weight gradients' operands across their leading
 // dimension (bank conflicts in the transposing LDS stores).  7-512-512-512-56
-// with a batch of 8192: 335 us a step -> 100 (row pass 52, weight gradients 38, the rest 9).
+// with a batch of 8192: 335 us a step -> 98 (row pass 50, weight gradients 38, the rest 9).
 #pragma once
 
 #include "sd_mlp.hpp"
@@ -147,18 +147,37 @@ __global__ __launch_bounds__(64 * RowGeo<H>::NW) void train_rows_kernel(TrainNet
     bf16x8 b0[1][NT], b[RING][NT];
     row_prefetch<NT, 1, 1>(b0, wf[0] + (size_t)wn * NT * 512);
 
-    // the batch's rows
-    for (int e = tid; e < TR_ROWS * 32; e += THREADS) {
-        const int r = e >> 5, u = e & 31;
-        const int64_t pos = T.pos0 + row0 + 4 * r, s = T.perm ? T.perm[pos] : pos;
-        const bool ok = s >= 0 && s < T.samples;
-        x0[e] = (__bf16)(ok && u < 7 ? T.x[s * 7 + u] : 0.f);
-    }
-    for (int e = tid; e < TR_ROWS * 64; e += THREADS) {
-        const int r = e >> 6, j = e & 63;
-        if (j >= T.n) continue;
-        const int64_t pos = T.pos0 + row0 + 4 * r, s = T.perm ? T.perm[pos] : pos;
-        qs[r * T.n + j] = s >= 0 && s < T.samples ? T.q[s * T.qs + j * T.qj] : 0.f;
+    // the batch's rows: all sample numbers first, then all values, so that a
+    // thread waits for memory twice and not twice per value
+    {
+        constexpr int NX = TR_ROWS * 32 / THREADS, NQ = TR_ROWS * 64 / THREADS;
+        auto sample = [&](int r) -> int64_t {
+            const int64_t pos = T.pos0 + row0 + 4 * r;
+            return T.perm ? T.perm[pos] : pos;
+        };
+        int64_t sx[NX], sq[NQ];
+        float vx[NX], vq[NQ];
+#pragma unroll
+        for (int i = 0; i < NX; ++i) sx[i] = sample((tid + i * THREADS) >> 5);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) sq[i] = sample((tid + i * THREADS) >> 6);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int u = (tid + i * THREADS) & 31;
+            vx[i] = sx[i] >= 0 && sx[i] < T.samples && u < 7 ? T.x[sx[i] * 7 + u] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int j = (tid + i * THREADS) & 63;
+            vq[i] = sq[i] >= 0 && sq[i] < T.samples && j < T.n ? T.q[sq[i] * T.qs + j * T.qj] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) x0[tid + i * THREADS] = (__bf16)vx[i];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int e = tid + i * THREADS, j = e & 63;
+            if (j < T.n) qs[(e >> 6) * T.n + j] = vq[i];
+        }
     }
     __syncthreads();
     store_rows(A.in[0], x0, 32, 32);
