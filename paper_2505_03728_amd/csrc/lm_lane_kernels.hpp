@@ -25,11 +25,10 @@ namespace lane {
 // joints fit two per SIMD (longer ones need more than 256 registers), which
 // takes less than twice as long as one, and the per-lane kernel's time hardly
 // depends on the batch up to 65536.  30 iterations with early exit, four
-// lanes against one, us: 7 joints 87.5 / 131.1 at 16384, 124.1 / 137.5 at
-// 32768, 181.5 / 135.8 at 49152; 3 joints 61.7 / 89.1, 82.6 / 83.7, 109.5 /
-// 83.5; 10 joints 118.3 / 224.2, 228.0 / 204.3; without the rest term (the
-// redundant chains' steps then end in the FP64 re-solve) 7 joints 113.3 /
-// 219.1, 142.9 / 216.4, 213.8 / 232.1.
+// lanes against one, us: 7 joints 83 / 125 at 16384, 127 / 129 at 32768 (181.5 /
+// 135.8 at 49152 in an earlier build); 6 joints 78 / 111, 117 / 115; 10 joints
+// 112 / 192, 189 / 192; without the rest term (the redundant chains' steps then
+// end in the FP64 re-solve) 7 joints 97 / 180, 149 / 209.
 inline int64_t quad_max_problems(int chain_len) { return chain_len <= 8 ? 32768 : 16384; }
 // (target_exit is defined on the per-lane kernel's runs of lanes.)
 inline bool takes_quad(int chains, int chain_len, const SolveParams &P)

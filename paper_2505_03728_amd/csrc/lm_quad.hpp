@@ -22,12 +22,12 @@
 // bit for bit.  Control flow is uniform over a quad: a lane that reads
 // another by quad_perm finds it active.
 //
-// Bound: one wavefront's instruction stream (about 1.3 k instructions per
+// Bound: one wavefront's instruction stream (about 1.2 k instructions per
 // iteration for 7 joints, and the latencies that one wavefront per SIMD does
 // not hide).  Against one lane per problem, 30 iterations: 8 problems of 7
-// joints 145.8 -> 91.5 us; 16384 of the mobile base (10 joints) 226.3 ->
-// 115.4; 16384 of 7 joints without the rest term, where most steps end in the
-// FP64 re-solve, 219.1 -> 113.3 (183.0 with the per-lane kernel's re-solve).
+// joints 135 -> 84 us; 16384 of the mobile base (10 joints) 192 -> 112; 16384 of
+// 7 joints without the rest term, where most steps end in the FP64 re-solve,
+// 180 -> 97.
 #pragma once
 
 #include "lm_lane_kernels.hpp"
