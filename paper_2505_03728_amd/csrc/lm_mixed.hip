@@ -16,8 +16,9 @@
 // their own (128 VGPRs, 9.4 KiB, two row lengths, the LDS slice of unknown
 // alignment: 32-bit accesses); 935 with the slice's alignment and the robot in
 // constant memory known; 833 at their own row length.  With 60000 arms and
-// 20000 hands the batch took 2246, 1390 with these launches, 1134 with the hands
-// on four lanes per problem (lm_star.hpp).
+// 20000 hands the batch took 2246, 1390 with these launches, 1129 with the hands
+// on four lanes per problem (lm_star.hpp), 1121 with grids no larger than the
+// items.
 //
 // Method: Sec. III-A (LM over the sum of squared weighted residuals) for each
 // problem, as in the per-lane and per-wavefront kernels it instantiates.
@@ -170,6 +171,8 @@ int mixed_lds_floats(int path)
     }
 }
 
+int64_t items_of(const MixedGroup &G) { return (G.P.N + G.per_item - 1) / G.per_item; }
+
 // The launch of the batch's LAUNCH groups (from g0, which moves past them),
 // with the LDS of the largest of their paths.
 template <int LAUNCH>
@@ -177,14 +180,21 @@ hipError_t launch_groups(const MixedArgs &a, int &g0, int32_t *item_end, int32_t
                          hipStream_t s)
 {
     int ldsf = 0, g1 = g0;
-    for (; g1 < a.n_groups && (LAUNCH == PK_MIX_ALL || mixed_launch_of(a.g[g1].path) == LAUNCH); ++g1)
+    int64_t items = 0;
+    for (; g1 < a.n_groups && (LAUNCH == PK_MIX_ALL || mixed_launch_of(a.g[g1].path) == LAUNCH); ++g1) {
         ldsf = std::max(ldsf, mixed_lds_floats(a.g[g1].path));
+        items += items_of(a.g[g1]);
+    }
     if (g1 == g0) return hipSuccess;
     const int first = g0;
     int32_t *head = heads + LAUNCH % PK_MIX_LAUNCHES;
     g0 = g1;
+    // No more wavefronts than items: the dispatcher spreads a grid over the SIMDs,
+    // but which of too many wavefronts reach the queue first is chance, and two
+    // items on one SIMD leave another idle (60000 arms, 938 items: 302 us from a
+    // grid of 2048, 227 from one of 938).
     const int wpb = wg / 64;
-    const dim3 grid(nblk(waves, wpb)), block(wg);
+    const dim3 grid(nblk(std::min<int64_t>(waves, items), wpb)), block(wg);
     const size_t lds = (size_t)wpb * ldsf * sizeof(float);
     switch (wg) {
     case 64:
