@@ -13,8 +13,7 @@ bool lane_variant_available(int chains, int chain_len, int kind)
 
 bool lane_takes_best(const RobotC &h, const SolveParams &P)
 {
-    return 64 % P.K == 0 || (P.K <= 64 && (lane::takes_quad(h.chains, h.chain_len, P) ||
-                                           lane::takes_star(h.chains, h.chain_len, P)));
+    return lane::takes_best(h.chains, h.chain_len, h.e[0].kind, P);
 }
 
 hipError_t launch_lm_lane(const RobotC *dev_robot, const RobotC &h, const SolveParams &P,

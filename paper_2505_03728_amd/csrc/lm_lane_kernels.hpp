@@ -4,6 +4,7 @@
 // queue.
 #pragma once
 
+#include "lane_rule.hpp"
 #include "lm_lane.hpp"
 
 namespace pk {
@@ -19,31 +20,6 @@ inline hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blo
 }
 
 namespace lane {
-
-// Single-chain batches up to this size run with four lanes per problem: at
-// 16384 problems the quads give every SIMD one wavefront; chains of up to 8
-// joints fit two per SIMD (longer ones need more than 256 registers), which
-// takes less than twice as long as one, and the per-lane kernel's time hardly
-// depends on the batch up to 65536.  30 iterations with early exit, four
-// lanes against one, us: 7 joints 83 / 125 at 16384, 127 / 129 at 32768 (181.5 /
-// 135.8 at 49152 in an earlier build); 6 joints 78 / 111, 117 / 115; 10 joints
-// 112 / 192, 189 / 192; without the rest term (the redundant chains' steps then
-// end in the FP64 re-solve) 7 joints 97 / 180, 149 / 209.
-inline int64_t quad_max_problems(int chain_len) { return chain_len <= 8 ? 32768 : 16384; }
-// (target_exit is defined on the per-lane kernel's runs of lanes.)
-inline bool takes_quad(int chains, int chain_len, const SolveParams &P)
-{
-    return chains == 1 && !P.target_exit && P.N <= quad_max_problems(chain_len);
-}
-
-// The star of four chains of four joints with position EEs runs with four lanes
-// per problem, a chain each (lm_star.hpp: faster at every size measured, 64 to a
-// million problems); the per-lane kernel keeps target_exit, which is defined on
-// its runs of lanes.
-inline bool takes_star(int chains, int chain_len, const SolveParams &P)
-{
-    return chains == 4 && chain_len == 4 && !P.target_exit;
-}
 
 // Next work item of this block: the block index for a plain grid, else an
 // atomic pop from the device queue (block = one wavefront).
@@ -149,7 +125,7 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
     int64_t grid = (P.N + block - 1) / block;
     const bool persist = P.queue_head != nullptr;
     if constexpr (C == 1) {
-        if (!persist && !P.active && !P.n_active && !P.st_state && takes_quad(C, L, P))
+        if (!persist && !P.active && !P.n_active && !P.st_state && takes_quad(C, L, ee_of(KIND), P, best != nullptr))
             return quad::launch<L, KIND>(rb, P, s, best);
     }
     if constexpr (C == 4) {

@@ -40,7 +40,7 @@ using lane::LaneFinal;
 using lane::LaneLds;
 using lane::pris_of;
 
-constexpr int PROBLEMS = 64;             // per workgroup
+constexpr int PROBLEMS = lane::QUAD_PROBLEMS;
 constexpr int THREADS = 4 * PROBLEMS;
 
 // v of lane S of the quad.
@@ -548,7 +548,7 @@ hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const B
     const float *qr = P.q_rest ? P.q_rest : rb->mid;
     if (best && P.K > PROBLEMS) return hipErrorInvalidValue;
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
-    const int per_block = best ? PROBLEMS / P.K * P.K : PROBLEMS;
+    const int per_block = lane::quad_per_block(P.K, best != nullptr);
     const dim3 grid((unsigned)((P.N + per_block - 1) / per_block));
     hipLaunchKernelGGL((lm_quad_kernel<L, KIND>), grid, dim3(THREADS), 0, s, rb, qr, P, B, per_block);
     return hipGetLastError();

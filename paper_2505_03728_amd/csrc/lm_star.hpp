@@ -26,7 +26,7 @@ using quad::quad_max;
 
 constexpr int C = 4, L = 4, N = C * L, ROWS = 3, NA = L * (L + 1) / 2;
 constexpr int KIND = PK_EE_POSITION;
-constexpr int PROBLEMS = 64;             // per workgroup
+constexpr int PROBLEMS = lane::QUAD_PROBLEMS;
 constexpr int THREADS = 4 * PROBLEMS;
 
 PK_DEV bool quad_all(bool v)
@@ -378,7 +378,7 @@ inline hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blo
         return hipGetLastError();
     }
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
-    const int per_block = best ? PROBLEMS / P.K * P.K : PROBLEMS;
+    const int per_block = lane::quad_per_block(P.K, best != nullptr);
     const dim3 grid((unsigned)((P.N + per_block - 1) / per_block));
     hipLaunchKernelGGL(lm_star_kernel, grid, dim3(THREADS), 0, s, rb, qr, P, B, per_block);
     return hipGetLastError();
