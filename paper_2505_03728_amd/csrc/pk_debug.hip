@@ -1,7 +1,7 @@
 // Batched forward kinematics, residual/Jacobian (parity entry points) and
 // the best-of-K selection.  One problem per thread, any tree up to
-// PK_MAX_JOINTS joints; frames live in per-thread arrays.  The per-joint and
-// per-EE arithmetic is the same device code the LM kernels run.
+// PK_MAX_JOINTS joints.  The per-joint and per-EE arithmetic is the same device
+// code the LM kernels run.
 #include <math.h>
 
 #include "pk_device.hpp"
@@ -37,14 +37,14 @@ PK_DEV void fk_all(const RobotC *__restrict__ rb, const float *q, int64_t N, int
     }
 }
 
-// Forward kinematics, one configuration per lane.  The joints are walked in
-// order with the running frame in registers; the frames that a later branch
-// starts from (build_fk_plan) are kept in LDS, 12 floats per lane and slot.
+// Forward kinematics, one configuration per lane.  The joints are walked
+// depth first (build_fk_plan) with the running frame in registers; the frames
+// that a later branch starts from are kept in LDS, 12 floats per lane and slot.
 // Bound: HBM (28 bytes in and 28 out per configuration of a 7-joint arm),
 // with the VALU close behind (about 0.5 k instructions per configuration).
-// With every frame in a per-thread array, as before, each joint went through
-// scratch memory: a call on 1,000,003 arm configurations took 140.9 us, now
-// 24.3 us (2.3 TB/s).
+// With every frame in a per-thread array each joint went through scratch
+// memory: a call on 1,000,003 arm configurations took 140.9 us, now 20.6 us
+// (2.7 TB/s).
 constexpr int FK_BLOCK = 64;
 
 template <bool FRAMES>
@@ -58,11 +58,16 @@ __global__ __launch_bounds__(FK_BLOCK) void fk_kernel(const RobotC *__restrict__
     float *mine = saved + threadIdx.x;
     const int n = rb->n;
     float O[9], pos[3];
-    float qn = joint_value(rb, q, N, p, 0);
-    for (int j = 0; j < n; ++j) {
+    uint32_t next = rb->fk_step[0];
+    float qn = joint_value(rb, q, N, p, next & 0xff);
+    for (int i = 0; i < n; ++i) {
+        const uint32_t step = next, from = step >> 8 & 0xff, save = step >> 16 & 0xff;
+        const int j = step & 0xff;
         const float qj = qn;
-        if (j + 1 < n) qn = joint_value(rb, q, N, p, j + 1);   // in flight during this joint
-        const int from = rb->fk_from[j];
+        if (i + 1 < n) {
+            next = rb->fk_step[i + 1];
+            qn = joint_value(rb, q, N, p, next & 0xff);   // in flight during this joint
+        }
         if (from == PK_FK_BASE) {
 #pragma unroll
             for (int u = 0; u < 9; ++u) O[u] = u % 4 == 0 ? 1.f : 0.f;
@@ -84,7 +89,6 @@ __global__ __launch_bounds__(FK_BLOCK) void fk_kernel(const RobotC *__restrict__
         for (int u = 0; u < 9; ++u) O[u] = On[u];
 #pragma unroll
         for (int u = 0; u < 3; ++u) pos[u] = pn[u];
-        const int save = rb->fk_save[j];
         if (save != PK_FK_NONE) {
             float *dst = mine + save * 12 * FK_BLOCK;
 #pragma unroll
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(FK_BLOCK) void fk_kernel(const RobotC *__restrict__
 #pragma unroll
             for (int u = 0; u < 3; ++u) dst[(9 + u) * N] = pos[u];
         }
-        for (unsigned ees = rb->fk_ees[j]; ees; ees &= ees - 1) {
+        for (unsigned ees = step >> 24; ees; ees &= ees - 1) {
             const int k = __builtin_ctz(ees);
             float R[9], pe[3], w, x, y, z;
             ee_frame(O, pos, rb->e[k].G, rb->e[k].t, R, pe);
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(256) void best_of_k_kernel(int64_t T, int32_t K, in
 hipError_t launch_fk(const RobotC *rb, const RobotC &host, int64_t N, const float *q, float *ee_pose,
                      float *joint_frames, hipStream_t s)
 {
-    // at most PK_FK_MAX_SLOTS slots of 3 KB: 96 KB of the CU's 160
+    // at most PK_FK_MAX_SLOTS slots of 3 KB
     const size_t lds = (size_t)host.fk_slots * 12 * FK_BLOCK * sizeof(float);
     const dim3 grid((unsigned)((N + FK_BLOCK - 1) / FK_BLOCK)), block(FK_BLOCK);
     if (joint_frames)

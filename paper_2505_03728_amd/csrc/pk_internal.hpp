@@ -44,12 +44,17 @@ constexpr int PK_LANE_MAX_CHAIN = 10; // longest single chain the per-lane kerne
 constexpr int PK_PATH_MAX_DEPTH = 16; // tree levels the path-pair wavefront kernel serves
 constexpr uint8_t PK_PATH_NONE = 0xff;
 
-// Forward-kinematics plan: where joint j's parent frame comes from (fk_from)
-// and where its own is kept (fk_save).
-constexpr int PK_FK_MAX_SLOTS = PK_MAX_JOINTS / 2;
-constexpr uint8_t PK_FK_RUN = 0xfe;    // fk_from: the frame just computed (joint j - 1)
-constexpr uint8_t PK_FK_BASE = 0xff;   // fk_from: the base
-constexpr uint8_t PK_FK_NONE = 0xff;   // fk_save: not kept
+// Forward-kinematics plan, a word per step: the joint of the step, where its
+// parent's frame comes from, where its own is kept, and the EEs on it (bit k:
+// EE k).
+constexpr int PK_FK_MAX_SLOTS = 5;        // see build_fk_plan
+constexpr uint32_t PK_FK_RUN = 0xfe;      // from: the frame just computed (the step before)
+constexpr uint32_t PK_FK_BASE = 0xff;     // from: the base
+constexpr uint32_t PK_FK_NONE = 0xff;     // save: not kept
+constexpr uint32_t fk_step_word(uint32_t joint, uint32_t from, uint32_t save, uint32_t ees)
+{
+    return joint | from << 8 | save << 16 | ees << 24;
+}
 
 // Path-pair layout of one problem on a 64-lane wavefront.  Lane l holds the
 // pair (joint[l], path group[l]): every joint on the path from the root to EE
@@ -102,9 +107,8 @@ struct RobotC {
     uint8_t step_of[PK_MAX_JOINTS];
     uint8_t step_pos[PK_MAX_JOINTS];
     PathC path;
-    int32_t fk_slots, pad3;                // saved frames live at once
-    uint8_t fk_from[PK_MAX_JOINTS], fk_save[PK_MAX_JOINTS];
-    uint8_t fk_ees[PK_MAX_JOINTS];         // bit k: EE k sits on this joint
+    int32_t fk_slots, pad3;                // slots of the plan
+    uint32_t fk_step[PK_MAX_JOINTS];       // fk_step_word of each step
 };
 
 // Uniform per-call data for the LM kernels (passed by value).

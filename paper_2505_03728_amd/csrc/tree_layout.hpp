@@ -1,7 +1,7 @@
-// Host-side tables of the tree factorisation: the leaves-first elimination
-// schedule and the path-pair layout (PathC) of the one-problem-per-wavefront
-// LM kernel.  Used by pk_robot_upload, and by the CPU test of the layout,
-// which solves random trees with these tables.
+// Host-side tables of a robot: the leaves-first elimination schedule and the
+// path-pair layout (PathC) of the one-problem-per-wavefront LM kernel, and the
+// forward-kinematics plan.  Used by pk_robot_upload, and by the CPU tests of the
+// tables, which solve and walk random trees with them.
 #pragma once
 
 #include <string.h>
@@ -41,35 +41,69 @@ inline void build_step_schedule(RobotC &R)
     R.nstep = ns;
 }
 
-// Forward-kinematics plan (R.fk_from, fk_save, fk_ees, fk_slots): joint j
-// continues from the frame of joint j - 1 when that is its parent, else from
-// a saved frame.  A frame is saved when some child is not the next joint, in
-// the lowest free slot, which is free again after the last such child.  A
-// live frame waits for a joint of its own, so at most PK_MAX_JOINTS / 2 are
-// live at once.  Needs R.n, R.m, the parents and the EEs' joints.
+// Forward-kinematics plan (R.fk_step, fk_slots): depth first, so that a joint
+// continues from the frame of the step before where that is its parent, else
+// from a saved frame.  A frame is saved when a child is not the next step, in
+// the lowest free slot, which is free again once the last child has read it.
+// A joint's child that needs the most slots comes last, when the joint's own
+// slot is free: then k slots at once need 2^k leaves (two children that need
+// k - 1 each), so 64 joints never need more than 5.  In the joints' order, which
+// may be breadth first, up to 32 frames waited, and at 96 KB of LDS a wavefront
+// had its CU for itself: 300,000 configurations of 32 chains of two joints 844 us
+// (371 with every frame in scratch memory), 53 now.
+// Needs R.n, R.m, the parents and the EEs' joints.
 inline void build_fk_plan(RobotC &R)
 {
-    int last[PK_MAX_JOINTS], slot_end[PK_FK_MAX_SLOTS];
-    for (int j = 0; j < R.n; ++j) {
-        last[j] = -1;
-        R.fk_ees[j] = 0;
+    const int n = R.n;
+    int need[PK_MAX_JOINTS], last_child[PK_MAX_JOINTS], second[PK_MAX_JOINTS];
+    for (int j = 0; j < n; ++j) last_child[j] = second[j] = -1;
+    for (int j = n - 1; j >= 0; --j) {   // (children have higher numbers)
+        const int lc = last_child[j];
+        need[j] = lc < 0 ? 0 : need[lc];
+        if (second[j] >= 0 && need[j] < need[second[j]] + 1) need[j] = need[second[j]] + 1;
         const int par = R.j[j].parent;
-        if (par >= 0 && par != j - 1) last[par] = j;
+        if (par < 0) continue;
+        if (last_child[par] < 0 || need[j] > need[last_child[par]]) {
+            second[par] = last_child[par];
+            last_child[par] = j;
+        } else if (second[par] < 0 || need[j] > need[second[par]]) {
+            second[par] = j;
+        }
+    }
+    int order[PK_MAX_JOINTS], step_of[PK_MAX_JOINTS], stack[PK_MAX_JOINTS], top = 0, steps = 0;
+    for (int j = n - 1; j >= 0; --j)
+        if (R.j[j].parent < 0) stack[top++] = j;
+    while (top > 0) {
+        const int j = stack[--top];
+        step_of[j] = steps;
+        order[steps++] = j;
+        if (last_child[j] >= 0) stack[top++] = last_child[j];
+        for (int c = n - 1; c > j; --c)
+            if (R.j[c].parent == j && c != last_child[j]) stack[top++] = c;
+    }
+    uint32_t ees[PK_MAX_JOINTS] = {0}, save[PK_MAX_JOINTS];
+    for (int k = 0; k < R.m; ++k) ees[R.e[k].joint] |= 1u << k;
+    int last_read[PK_MAX_JOINTS], slot_end[PK_FK_MAX_SLOTS];
+    for (int j = 0; j < n; ++j) last_read[j] = -1;
+    for (int j = 0; j < n; ++j) {
+        const int par = R.j[j].parent;
+        if (par >= 0 && step_of[j] != step_of[par] + 1 && step_of[j] > last_read[par]) last_read[par] = step_of[j];
     }
     for (int s = 0; s < PK_FK_MAX_SLOTS; ++s) slot_end[s] = -1;   // free
     R.fk_slots = 0;
-    for (int j = 0; j < R.n; ++j) {
-        const int par = R.j[j].parent;
-        R.fk_from[j] = par < 0 ? PK_FK_BASE : par == j - 1 ? PK_FK_RUN : R.fk_save[par];
-        R.fk_save[j] = PK_FK_NONE;
-        if (last[j] < 0) continue;
-        int s = 0;   // joint j reads its parent's frame before it saves its own
-        while (slot_end[s] > j) ++s;
-        slot_end[s] = last[j];
-        R.fk_save[j] = (uint8_t)s;
-        if (s + 1 > R.fk_slots) R.fk_slots = s + 1;
+    for (int i = 0; i < n; ++i) {
+        const int j = order[i], par = R.j[j].parent;
+        const uint32_t from = par < 0 ? PK_FK_BASE : step_of[par] == i - 1 ? PK_FK_RUN : save[par];
+        save[j] = PK_FK_NONE;
+        if (last_read[j] >= 0) {
+            int s = 0;   // the step reads its parent's frame before it saves its own
+            while (slot_end[s] > i) ++s;
+            slot_end[s] = last_read[j];
+            save[j] = (uint32_t)s;
+            if (s + 1 > R.fk_slots) R.fk_slots = s + 1;
+        }
+        R.fk_step[i] = fk_step_word((uint32_t)j, from, save[j], ees[j]);
     }
-    for (int k = 0; k < R.m; ++k) R.fk_ees[R.e[k].joint] |= (uint8_t)(1u << k);
 }
 
 // Path-pair layout (PathC) of the wavefront kernel that gives each (joint,
