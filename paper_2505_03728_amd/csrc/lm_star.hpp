@@ -351,18 +351,21 @@ static __global__ __launch_bounds__(THREADS) void lm_star_kernel(const RobotC *_
     }
 }
 
-// Persistent, resumable variant: wavefronts pop 16 problems of the active list
-// from P.queue_head until it is exhausted.
+// Persistent, resumable variant: wavefront w takes every gridDim-th 16 problems
+// of the active list, from the w-th on.  No queue: 16 problems are little work
+// for an atomic on one address (about 12 ns each, one after the other), and with
+// few iterations per launch the atomics were the launch.  100000 hands, 50
+// iterations in launches of 1, 2, 5 and 50, 16 wavefronts per CU, us: 7495, 3797,
+// 1610 and 403 from a queue; 3143, 1504, 760 and 368 now (4162, 2239, 1285 and
+// 859 with one lane per problem and 64 problems to a pop).
 static __global__ __launch_bounds__(64) void lm_star_persist_kernel(const RobotC *__restrict__ rb,
                                                                     const float *__restrict__ qr, SolveParams P)
 {
     const int64_t nact = P.n_active ? (int64_t)*P.n_active : P.N, nitems = (nact + 15) / 16;
-    int64_t item = lane::pop_item(P.queue_head);
-    while (item < nitems) {
+    for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
         const int64_t i = item * 16 + (threadIdx.x >> 2);
         Final fin;
         if (i < nact) star_problem<true>(rb, qr, P, i, &fin);
-        item = lane::pop_item(P.queue_head);
     }
 }
 
@@ -371,7 +374,7 @@ inline hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blo
 {
     const float *qr = P.q_rest ? P.q_rest : rb->mid;
     if (best && (P.K > PROBLEMS || P.queue_head || P.active || P.n_active)) return hipErrorInvalidValue;
-    if (P.queue_head) {
+    if (P.queue_head) {   // (the mark of a persistent launch)
         int64_t grid = (P.N + 15) / 16;
         if (persist_blocks > 0 && persist_blocks < grid) grid = persist_blocks;
         hipLaunchKernelGGL(lm_star_persist_kernel, dim3((unsigned)grid), dim3(64), 0, s, rb, qr, P);
