@@ -274,8 +274,8 @@ struct SeederState {
     float *Z = nullptr, *Y = nullptr, *dZ = nullptr, *dY = nullptr, *Q = nullptr, *part = nullptr;
     float *splitbuf = nullptr;          // split-K partial weight gradients
     size_t splitbuf_floats = 0;
-    // BF16 weights in MFMA fragment order for the fused inference pass,
-    // rebuilt from Pb after the parameters change.
+    // BF16 weights in MFMA fragment order for the fused passes.  wf_dirty: an
+    // inference builds Wf from Pb first (training builds both by itself).
     __bf16 *Wf = nullptr;
     __bf16 *Wt = nullptr;               // the same of the transposed weights (training)
     std::vector<int64_t> wfoff;
@@ -369,6 +369,15 @@ hipError_t forward(SeederState *s, int64_t rows, bool train, hipStream_t st)
                             EpiOut{s->P + s->boff[L], s->Y, s->out_pad}, st);
 }
 
+// Whether launches on st are recorded into a graph and not run.
+bool recorded(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Inference forward pass over `rows` rows of X0 into Y: the fused kernel for
 // the shapes it covers (hidden width 128, 256 or 512, padded output width
 // 64), else the layer-by-layer GEMMs.  Both give the same values.
@@ -388,7 +397,7 @@ hipError_t forward_infer(SeederState *s, int64_t rows, hipStream_t st)
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        s->wf_dirty = false;
+        s->wf_dirty = recorded(st);
     }
     MlpArgs a{};
     a.depth = s->depth;
@@ -820,7 +829,6 @@ int pk_seeder_grad(pk_ctx *ctx, int32_t id, const float *x, const float *q, int6
         const sd::TrainBatch b{x, q, s->n, 1, B, 0, nullptr, s->n, s->K};
         PK_HIP(ctx, train_fragments(t, st));
         PK_HIP(ctx, train_step(s, t, b, sd::AdamArgs{}, loss, st));
-        s->wf_dirty = false;
         return PK_OK;
     }
     hipLaunchKernelGGL(sd::load_rows_kernel, dim3(sd::blocks(B, 256)), dim3(256), 0, st, B, B, s->in_pad,
