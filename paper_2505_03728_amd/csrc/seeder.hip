@@ -297,46 +297,57 @@ void seeder_free(SeederState *s)
 
 namespace {
 
+// The three-launch training step (sd_train.hpp) serves up to 3 hidden layers
+// of width 128, 256 or 512; other shapes train layer by layer.
+bool train_fused(const SeederState *s)
+{
+    return s->in_pad == 32 && s->out_pad == 64 && (s->H == 128 || s->H == 256 || s->H == 512) &&
+           s->depth < sd::TR_MAX_LAYERS;
+}
+
+// Activations for `rows` rows, for inference and training alike: what the
+// shape's paths use.  The three-launch step keeps a gradient per layer and
+// pre-activations on chip, the layer-by-layer one a gradient in turn and every
+// pre-activation (width 512, 3 layers: 6.8 against 13.1 KB a row).
 int alloc_acts(pk_ctx *ctx, SeederState *s, int64_t rows)
 {
     if (rows <= s->cap) return PK_OK;
-    void *ptrs[] = {s->X0, s->Hb, s->dZb, s->dYb, s->Z, s->Y, s->dZ, s->dY, s->Q, s->part};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
     const int L = s->depth;
     const int64_t hsz = rows * s->H;
+    const bool fused = train_fused(s);
     bool ok = true;
-    ok &= hipMalloc(&s->X0, rows * s->in_pad * sizeof(__bf16)) == hipSuccess;
-    ok &= hipMalloc(&s->Hb, (size_t)L * hsz * sizeof(__bf16)) == hipSuccess;
-    ok &= hipMalloc(&s->dZb, (size_t)L * hsz * sizeof(__bf16)) == hipSuccess;
-    ok &= hipMalloc(&s->dYb, rows * s->out_pad * sizeof(__bf16)) == hipSuccess;
-    ok &= hipMalloc(&s->Z, (size_t)L * hsz * sizeof(float)) == hipSuccess;
-    ok &= hipMalloc(&s->Y, rows * s->out_pad * sizeof(float)) == hipSuccess;
-    ok &= hipMalloc(&s->dZ, hsz * sizeof(float)) == hipSuccess;
-    ok &= hipMalloc(&s->dY, rows * s->out_pad * sizeof(float)) == hipSuccess;
-    ok &= hipMalloc(&s->Q, rows * s->n * sizeof(float)) == hipSuccess;
-    // column-sum partials (four per 128-row chunk) of every layer, the rows' losses
-    ok &= hipMalloc(&s->part, ((rows / sd::COLSUM_ROWS + 1) * (size_t)4 * (L * s->H + s->out_pad) + rows) *
-                                  sizeof(float) + 4096) == hipSuccess;
-    // Split-K partials: sized for the largest split any row count can pick.
+    auto renew = [&](auto *&p, size_t count) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+        if (count) ok &= hipMalloc(&p, count * sizeof(*p)) == hipSuccess;
+    };
+    s->cap = 0;
+    renew(s->X0, rows * s->in_pad);
+    renew(s->Hb, (size_t)L * hsz);
+    renew(s->dZb, (size_t)(fused ? L : 1) * hsz);
+    renew(s->dYb, rows * s->out_pad);
+    renew(s->Y, rows * s->out_pad);
+    renew(s->Z, fused ? 0 : (size_t)L * hsz);
+    renew(s->dZ, fused ? 0 : hsz);
+    renew(s->dY, fused ? 0 : rows * s->out_pad);
+    renew(s->Q, fused ? 0 : rows * s->n);
+    // fused: column-sum partials (four per 128-row chunk) of every layer, the
+    // rows' losses; else partials of a layer (one per chunk) or of the loss (one
+    // per 16 rows)
+    const size_t chunks = rows / sd::COLSUM_ROWS + 1;
+    renew(s->part, (fused ? chunks * 4 * (L * s->H + s->out_pad) + rows
+                          : chunks * std::max(s->H, s->out_pad) + rows / 16 + 1) + 1024);
+    // Split-K partials: sized for the largest split any row count can pick (of
+    // the first and the last layer at once, or of one layer in turn).
     size_t need = 0;
     for (int l = 0; l <= L; ++l) {
-        const int M = s->lout[l], N = s->lin[l];
-        need = std::max(need, (size_t)sd::split_max(M, N) * M * N);
+        const size_t floats = (size_t)sd::split_max(s->lout[l], s->lin[l]) * s->lout[l] * s->lin[l];
+        need = !fused ? std::max(need, floats) : l == 0 || l == L ? need + floats : need;
     }
-    need = std::max(need, (size_t)sd::split_max(s->out_pad, s->H) * s->out_pad * s->H +
-                              (size_t)sd::split_max(s->H, s->in_pad) * s->H * s->in_pad);
-    if (s->splitbuf) (void)hipFree(s->splitbuf);
-    s->splitbuf = nullptr;
     s->splitbuf_floats = 0;
-    if (hipMalloc(&s->splitbuf, need * sizeof(float)) == hipSuccess)
-        s->splitbuf_floats = need;
-    else
-        ok = false;
-    if (!ok) {
-        s->cap = 0;
-        return fail(ctx, PK_ENOMEM, "seeder: activation allocation for %lld rows failed", (long long)rows);
-    }
+    renew(s->splitbuf, need);
+    if (!ok) return fail(ctx, PK_ENOMEM, "seeder: activation allocation for %lld rows failed", (long long)rows);
+    s->splitbuf_floats = need;
     s->cap = rows;
     return PK_OK;
 }
@@ -549,7 +560,8 @@ int pk_seeder_create(pk_ctx *ctx, int32_t robot_id, int32_t K, int32_t hidden, i
         s->wfoff.push_back(wfn);
         wfn += (int64_t)s->lin[l] * s->lout[l];
     }
-    ok = ok && hipMalloc(&s->Wf, wfn * 2) == hipSuccess && hipMalloc(&s->Wt, wfn * 2) == hipSuccess;
+    ok = ok && hipMalloc(&s->Wf, wfn * 2) == hipSuccess &&
+         (!train_fused(s) || hipMalloc(&s->Wt, wfn * 2) == hipSuccess);
     if (!ok) {
         seeder_free(s);
         return fail(ctx, PK_ENOMEM, "pk_seeder_create: allocation failed");
@@ -641,14 +653,6 @@ hipError_t loss_and_grads(SeederState *s, int64_t rows, int64_t B, float *loss_l
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return backward(s, rows, st);
-}
-
-// The three-launch training step (sd_train.hpp) serves up to 3 hidden layers
-// of width 128, 256 or 512; other shapes train layer by layer.
-bool train_fused(const SeederState *s)
-{
-    return s->in_pad == 32 && s->out_pad == 64 && (s->H == 128 || s->H == 256 || s->H == 512) &&
-           s->depth < sd::TR_MAX_LAYERS;
 }
 
 struct TrainPlan {
