@@ -240,13 +240,15 @@ int pk_destroy(pk_ctx *ctx)
 {
     if (!ctx) return PK_OK;
     (void)hipSetDevice(ctx->device);
+    // calls may be in flight on any stream; graphs go before what they read
+    (void)hipDeviceSynchronize();
+    sched_free(ctx);
     for (auto &r : ctx->robots)
         if (r.dev) (void)hipFree(r.dev);
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->ws2) (void)hipFree(ctx->ws2);
     if (ctx->ws3) (void)hipFree(ctx->ws3);
     for (auto *sd : ctx->seeders) seeder_free(sd);
-    sched_free(ctx);
     delete ctx;
     return PK_OK;
 }

@@ -149,8 +149,14 @@ int path_of(const RobotC &H, int variant)
     return MIX_WAVE_16_4;
 }
 
+// A graph execution, and the buffers that its launches read, may still be in use
+// by a replay on any stream: wait before either goes.  (Rare: a larger batch than
+// before, more than 8 batches or 16 schedules in turn, the end of the context.)
+void wait_for_replays() { (void)hipDeviceSynchronize(); }
+
 void drop_graphs(SchedCache &C)
 {
+    if (!C.graphs.empty()) wait_for_replays();
     for (auto &ge : C.graphs)
         if (ge.exec) (void)hipGraphExecDestroy(ge.exec);
     C.graphs.clear();
@@ -298,6 +304,7 @@ int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vec
     }
     if (C.tables.size() >= 8) {
         // the oldest entry goes, with the graphs built on it
+        wait_for_replays();
         const std::string old = C.tables.front().key + "#";
         for (size_t i = 0; i < C.graphs.size();)
             if (C.graphs[i].key.compare(0, old.size(), old) == 0) {
@@ -513,6 +520,7 @@ int run(pk_ctx *ctx, int n_groups, const pk_ik_group *groups, const pk_lm_option
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) return fail(ctx, PK_EHIP, "pk_ik_solve_mixed: instantiate: %s", hipGetErrorString(e));
     if (C.graphs.size() >= 16) {
+        wait_for_replays();
         (void)hipGraphExecDestroy(C.graphs.front().exec);
         C.graphs.erase(C.graphs.begin());
     }
