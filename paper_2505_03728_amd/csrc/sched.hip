@@ -238,7 +238,7 @@ int build_plans(pk_ctx *ctx, SchedCache &C, int n_groups, const pk_ik_group *gro
 }
 
 // Key of everything a batch's device table and graph bake in, except the
-// schedule.
+// schedule (numbers exactly: %a, not rounded).
 std::string data_key(int n_groups, const pk_ik_group *groups, const pk_lm_options *opt,
                      const std::vector<GroupPlan> &plans)
 {
@@ -253,11 +253,11 @@ std::string data_key(int n_groups, const pk_ik_group *groups, const pk_lm_option
                  (void *)go.iters_to_tol, (void *)go.best_index, (void *)go.best_joints,
                  (void *)go.target_success, (void *)groups[g].weights.q_rest);
         key += kb;
-        snprintf(kb, sizeof kb, "%g,%g,%g,%g,p%d;", groups[g].weights.w_pos, groups[g].weights.w_rot,
+        snprintf(kb, sizeof kb, "%a,%a,%a,%a,p%d;", groups[g].weights.w_pos, groups[g].weights.w_rot,
                  groups[g].weights.w_limit, groups[g].weights.w_rest, plans[g].path);
         key += kb;
     }
-    snprintf(kb, sizeof kb, "|%d,%d,%g,%g,%g,%g,%g,%g,%g,%g,%g", opt->max_iters, opt->early_exit,
+    snprintf(kb, sizeof kb, "|%d,%d,%a,%a,%a,%a,%a,%a,%a,%a,%a", opt->max_iters, opt->early_exit,
              opt->lambda0, opt->nu_up, opt->nu_down, opt->lambda_min, opt->lambda_max, opt->tol_pos,
              opt->tol_rot, opt->damping_floor, opt->pivot_rel);
     return key + kb;
