@@ -238,7 +238,8 @@ int build_plans(pk_ctx *ctx, SchedCache &C, int n_groups, const pk_ik_group *gro
 }
 
 // Key of everything a batch's device table and graph bake in, except the
-// schedule (numbers exactly: %a, not rounded).
+// schedule (numbers exactly: %a, not rounded; groups without a path in the single
+// launch all have the same one and differ by variant).
 std::string data_key(int n_groups, const pk_ik_group *groups, const pk_lm_options *opt,
                      const std::vector<GroupPlan> &plans)
 {
@@ -253,8 +254,8 @@ std::string data_key(int n_groups, const pk_ik_group *groups, const pk_lm_option
                  (void *)go.iters_to_tol, (void *)go.best_index, (void *)go.best_joints,
                  (void *)go.target_success, (void *)groups[g].weights.q_rest);
         key += kb;
-        snprintf(kb, sizeof kb, "%a,%a,%a,%a,p%d;", groups[g].weights.w_pos, groups[g].weights.w_rot,
-                 groups[g].weights.w_limit, groups[g].weights.w_rest, plans[g].path);
+        snprintf(kb, sizeof kb, "%a,%a,%a,%a,p%d.v%d;", groups[g].weights.w_pos, groups[g].weights.w_rot,
+                 groups[g].weights.w_limit, groups[g].weights.w_rest, plans[g].path, plans[g].variant);
         key += kb;
     }
     snprintf(kb, sizeof kb, "|%d,%d,%a,%a,%a,%a,%a,%a,%a,%a,%a", opt->max_iters, opt->early_exit,

@@ -1,11 +1,13 @@
 """The scheduler keeps a batch's description and graphs by what the call
-passes: a call that differs in one number's last bits is not the one before it."""
+passes: a call that differs in one number's last bits, or in a group's lanes per
+problem, is not the one before it."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
 from tests.gpu_util import soa, targets_dev
+from tests.test_gpu_wave import _hand5
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -57,3 +59,21 @@ def test_numbers_by_their_bits(ctx, mode, graph, name):
         for k in KEYS:
             assert np.array_equal(got[k], refs[-1][k], equal_nan=True), (x, k)
     assert not np.array_equal(refs[0]["cost"], refs[1]["cost"])
+
+
+def test_lanes_per_problem(ctx):
+    import torch
+
+    import paper_2505_03728_amd as pk
+    rid, targets, seeds = _problems(ctx, _hand5(), 64)
+    out = ctx.alloc_outputs(rid, 64, 1)
+    w, refs = pk.Weights(w_pos=10.0, w_rest=0.01), []
+    for variant in (pk.VARIANT_WAVE, pk.VARIANT_WAVE_JOINT):
+        refs.append(_plain(ctx, rid, targets, seeds, w, pk.Options(max_iters=6, variant=variant)))
+        ctx.ik_solve_mixed([{"rid": rid, "targets": targets, "seeds": seeds, "K": 1, "weights": w, "out": out}],
+                           pk.Options(max_iters=6), waves_per_cu=4, variants=[variant], mode=pk.SCHED_PER_GROUP)
+        torch.cuda.synchronize()
+        got = _host(out)
+        for k in KEYS:
+            assert np.array_equal(got[k], refs[-1][k], equal_nan=True), (variant, k)
+    assert not np.array_equal(refs[0]["joints"], refs[1]["joints"])
