@@ -15,6 +15,7 @@ struct RobotEntry {
 
 struct SeederState;
 void seeder_free(SeederState *s);
+struct SchedCache;        // sched.hip
 
 }  // namespace pk
 
@@ -23,6 +24,7 @@ struct pk_ctx {
     std::string err;
     std::vector<pk::RobotEntry> robots;
     std::vector<pk::SeederState *> seeders;
+    pk::SchedCache *sched = nullptr;   // mixed batches: descriptions, graphs, tuned schedules
     void *ws = nullptr;
     size_t ws_bytes = 0;
     void *ws2 = nullptr;      // learned-seed pipeline workspace

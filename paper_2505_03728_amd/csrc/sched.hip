@@ -67,6 +67,9 @@ struct Tuned {
     float ms;
 };
 
+}  // namespace
+
+// What a context keeps for its mixed batches (pk_ctx::sched).
 struct SchedCache {
     std::vector<TableEntry> tables;
     std::vector<GraphEntry> graphs;
@@ -79,7 +82,13 @@ struct SchedCache {
     std::vector<hipEvent_t> joins;
 };
 
-std::map<pk_ctx *, SchedCache> g_sched;
+namespace {
+
+SchedCache &cache_of(pk_ctx *ctx)
+{
+    if (!ctx->sched) ctx->sched = new SchedCache;
+    return *ctx->sched;
+}
 
 int cu_count(pk_ctx *ctx)
 {
@@ -462,7 +471,7 @@ hipError_t enqueue(pk_ctx *ctx, SchedCache &C, const TableEntry &te, std::vector
 int run(pk_ctx *ctx, int n_groups, const pk_ik_group *groups, const pk_lm_options *opt,
         const pk_sched_options &sch, hipStream_t stream)
 {
-    SchedCache &C = g_sched[ctx];
+    SchedCache &C = cache_of(ctx);
     std::vector<GroupPlan> plans;
     int rc = build_plans(ctx, C, n_groups, groups, opt, sch, plans);
     if (rc) return rc;
@@ -610,15 +619,15 @@ int sched_run(pk_ctx *ctx, int n_groups, const pk_ik_group *groups, const pk_lm_
 
 void sched_free(pk_ctx *ctx)
 {
-    auto it = g_sched.find(ctx);
-    if (it == g_sched.end()) return;
-    SchedCache &C = it->second;
+    if (!ctx->sched) return;
+    SchedCache &C = *ctx->sched;
     drop_tables(C);
     for (auto s : C.streams) (void)hipStreamDestroy(s);
     for (auto e : C.joins) (void)hipEventDestroy(e);
     if (C.fork) (void)hipEventDestroy(C.fork);
     if (C.buf) (void)hipFree(C.buf);
-    g_sched.erase(it);
+    delete ctx->sched;
+    ctx->sched = nullptr;
 }
 
 void sched_load_env(pk_ctx *ctx)
@@ -626,7 +635,7 @@ void sched_load_env(pk_ctx *ctx)
     const char *path = getenv("PK_AUTOTUNE_TABLE");
     if (path && *path) {
         const std::string err = ctx->err;
-        (void)load_table(ctx, g_sched[ctx], path);   // a missing file is not an error here
+        (void)load_table(ctx, cache_of(ctx), path);   // a missing file is not an error here
         ctx->err = err;
     }
 }
@@ -651,7 +660,7 @@ int pk_ik_solve_mixed(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
         for (int g = 0; g < n_groups; ++g)
             if (!robot_of(ctx, groups[g].robot_id))
                 return fail(ctx, PK_ENOTFOUND, "pk_ik_solve_mixed: group %d: unknown robot", g);
-        auto &C = g_sched[ctx];
+        auto &C = cache_of(ctx);
         auto it = C.tuned.find(tune_key(ctx, n_groups, groups, opt));
         if (it != C.tuned.end()) {
             const int ug = s.use_graph;
@@ -763,7 +772,7 @@ int pk_autotune_mixed(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
-    SchedCache &C = g_sched[ctx];
+    SchedCache &C = cache_of(ctx);
     C.tuned[tune_key(ctx, n_groups, groups, opt)] = Tuned{bo, bestt};
     *best = bo;
     if (best_ms) *best_ms = bestt;
@@ -778,13 +787,13 @@ int pk_autotune_mixed(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
 int pk_autotune_save(pk_ctx *ctx, const char *path)
 {
     if (!ctx || !path) return fail(ctx, PK_EINVAL, "pk_autotune_save: NULL argument");
-    return save_table(ctx, g_sched[ctx], path);
+    return save_table(ctx, cache_of(ctx), path);
 }
 
 int pk_autotune_load(pk_ctx *ctx, const char *path, int32_t *entries)
 {
     if (!ctx || !path) return fail(ctx, PK_EINVAL, "pk_autotune_load: NULL argument");
-    const int n = load_table(ctx, g_sched[ctx], path);
+    const int n = load_table(ctx, cache_of(ctx), path);
     if (n < 0) return n;
     if (entries) *entries = n;
     return PK_OK;
@@ -799,7 +808,7 @@ int pk_autotune_lookup(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
     for (int g = 0; g < n_groups; ++g)
         if (!robot_of(ctx, groups[g].robot_id))
             return fail(ctx, PK_ENOTFOUND, "pk_autotune_lookup: group %d: unknown robot", g);
-    auto &C = g_sched[ctx];
+    auto &C = cache_of(ctx);
     auto it = C.tuned.find(tune_key(ctx, n_groups, groups, opt));
     if (it == C.tuned.end()) return fail(ctx, PK_ENOTFOUND, "pk_autotune_lookup: no entry");
     *found = it->second.s;
