@@ -12,6 +12,7 @@
 //     the smoothness rows by ~1e5 in J^T J, and at that conditioning an FP32
 //     factorisation steers LM off the FP64 path (FP64 FMAs issue at the
 //     unpacked FP32 rate).
+#include <stddef.h>
 #include <string.h>
 
 #include <cmath>
@@ -71,6 +72,14 @@ struct TrajLds {
     // the band before it discards them: up to 64 past its end, and up to 16
     // rows before its start (the arrays above).
     double band[TRAJ_VMAX * W + 64];
+    // What those indices rely on: masked stores reach the dump from invd and from
+    // b, and the backward solve's last chunk reads 15 rows of diagonals above row 0.
+    static constexpr bool laid_out()
+    {
+        return offsetof(TrajLds, invd) == offsetof(TrajLds, b) + sizeof(b) &&
+               offsetof(TrajLds, dump) == offsetof(TrajLds, invd) + sizeof(invd) &&
+               offsetof(TrajLds, band) >= 15 * (W + 1) * sizeof(double) && offsetof(TrajLds, band) % sizeof(double) == 0;
+    }
 };
 
 PK_DEV float wsum(float v)
@@ -454,6 +463,7 @@ template <int NJ>
 PK_DEV bool band_solve(TrajLds<NJ> &S, int V, float thresh_rel, const int (&mpb)[Pairs<NJ>::PB], int tid)
 {
     constexpr int HB = TrajLds<NJ>::HB, W = TrajLds<NJ>::W, NR = NJ + HB, NX = TrajLds<NJ>::NX, CH = 16;
+    static_assert(TrajLds<NJ>::laid_out(), "indices beside b, invd and band stay in S");
     static_assert(NR + NJ <= 64, "the windows of a block and the next fit one wavefront");
     static_assert(HB + CH < 64, "a finished row's lane takes its next row before that is updated");
     double *band = S.band, *rhs = S.b, *invd = S.invd;
