@@ -52,7 +52,7 @@ struct TableEntry {
     std::string key;                 // buffers, weights, options, paths
     MixedArgs base;                  // the batch for the single launch (per-round fields unset)
     int32_t *dev = nullptr;          // item_end [PK_MIX_GROUPS], then the queue heads
-    int lds_floats = 0;              // mixed_lds_limit, largest over the batch's paths
+    int lds_floats = 0;              // per wavefront, largest over the batch's paths
     int max_n = 0;
     bool single_ok = false;          // every group has a path in the single launch
 };
@@ -306,7 +306,7 @@ int table_for(pk_ctx *ctx, SchedCache &C, const std::string &key, const std::vec
                 G.count = pl.counters;
                 G.path = pl.path;
                 G.per_item = wave ? 1 : pl.path == MIX_STAR_HAND ? 16 : 64;
-                te.lds_floats = std::max(te.lds_floats, mixed_lds_limit(pl.path));
+                te.lds_floats = std::max(te.lds_floats, mixed_lds_floats(pl.path));
                 te.max_n = std::max(te.max_n, (int)pl.P.N);
             }
         if (hipMalloc(&te.dev, 256) != hipSuccess)
@@ -736,7 +736,7 @@ int pk_autotune_mixed(pk_ctx *ctx, int32_t n_groups, const pk_ik_group *groups,
             const int path = path_of(robot_of(ctx, groups[g].robot_id)->host,
                                      vs[g] == PK_VARIANT_WAVE ? PK_VARIANT_WAVE : PK_VARIANT_LANE);
             single = single && path != MIX_WAVE_64_8;
-            if (path != MIX_WAVE_64_8) ldsf = std::max(ldsf, mixed_lds_limit(path));
+            if (path != MIX_WAVE_64_8) ldsf = std::max(ldsf, mixed_lds_floats(path));
         }
         for (int mode : {PK_SCHED_SINGLE, PK_SCHED_PER_GROUP})
         for (int k : ks)

@@ -64,14 +64,6 @@ struct MixedArgs {
 // LDS floats one wavefront needs on a path.
 int mixed_lds_floats(int path);
 
-// LDS floats per wavefront that decide which workgroup sizes a batch is served
-// with.  The star uses none, but its groups keep the sizes of the per-lane
-// kernel that served them before it (104 slots of 64 lanes).
-inline int mixed_lds_limit(int path)
-{
-    return path == MIX_STAR_HAND ? 104 * 64 : mixed_lds_floats(path);
-}
-
 // Enqueues one round on stream s: plan (work items per group into item_end,
 // queue heads reset), persistent solves (each problem at most P.iter_budget
 // more iterations), and, unless it is the last round, compaction.  a holds
