@@ -15,8 +15,7 @@ template <int L, int KIND>
 hipError_t launch(const RobotC *rb, const SolveParams &P, hipStream_t s, const BestOut *best);
 }
 namespace star {
-inline hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blocks, hipStream_t s,
-                         const BestOut *best);
+hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blocks, hipStream_t s, const BestOut *best);
 }
 
 namespace lane {
@@ -137,15 +136,20 @@ hipError_t launch_star(const RobotC *rb, const SolveParams &P, int persist_block
     const dim3 g((unsigned)grid), b(block);
     if (best && (persist || P.active || P.n_active || 64 % P.K != 0)) return hipErrorInvalidValue;
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
-    if (persist && P.target_exit)
-        hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P);
-    else if (P.target_exit)
-        hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P, B);
-    else if constexpr (C == 1) {
-        if (persist)
+    if constexpr (C == 1) {
+        if (persist && P.target_exit)
+            hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P);
+        else if (persist)
             hipLaunchKernelGGL((lm_lane_persist_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P);
+        else if (P.target_exit)
+            hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P, B);
         else
             hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, false>), g, b, 0, s, rb, qr, P, B);
+    } else {
+        // (the star kernel takes all else; no persistent launch has target_exit
+        // with more than one EE)
+        if (persist) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((lm_lane_kernel<C, L, KIND, true>), g, b, 0, s, rb, qr, P, B);
     }
     return hipGetLastError();
 }
@@ -164,4 +168,3 @@ hipError_t launch_lane_chain_c(int L, int kind, const RobotC *rb, const SolvePar
 }  // namespace pk
 
 #include "lm_quad.hpp"
-#include "lm_star.hpp"

@@ -24,8 +24,8 @@
 // problem, as in the per-lane and per-wavefront kernels it instantiates.
 #include <algorithm>
 
-#include "lm_lane_kernels.hpp"
 #include "lm_path.hpp"
+#include "lm_star.hpp"
 #include "lm_wave.hpp"
 #include "sched_table.hpp"
 
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(LAUNCH < 3 ?
                 wave::wave_problem<16, 4>(constant(G.rb), G.P, ws, first);
                 break;
             default:   // rows for any tree; only in the kernel with every path
+                static_assert(path::Lds<8, 4>::FLOATS == path::Lds<16, 4>::FLOATS, "mixed_lds_floats gives the tree's own");
                 if constexpr (LAUNCH == PK_MIX_ALL) run_path<16, 16>(G, g, ws, first);
                 break;
             }
@@ -170,6 +171,8 @@ int mixed_lds_floats(int path)
     default: return 0;
     }
 }
+
+namespace {
 
 int64_t items_of(const MixedGroup &G) { return (G.P.N + G.per_item - 1) / G.per_item; }
 
@@ -233,6 +236,8 @@ bool one_launch(const MixedArgs &a, int wpc, int cus, int wg)
     const int held = std::min(8, wpb * (160 * 1024 / block_lds));   // per CU (237 VGPRs: 2 per SIMD)
     return !same && trees <= (int64_t)std::min(wpc, held) * cus;
 }
+
+}  // namespace
 
 hipError_t launch_mixed_round(const MixedArgs &a, int32_t *item_end, int32_t *heads, int max_n,
                               bool last, int wpc, int cus, int wg, hipStream_t s)

@@ -67,18 +67,6 @@ PK_DEV T from(T v, int s)
     return s == 0 ? from<0>(v) : s == 1 ? from<1>(v) : s == 2 ? from<2>(v) : from<3>(v);
 }
 
-// v of the lane holding row (r + 1) mod 3, (r + 2) mod 3; lane 3 as lane 2.
-PK_DEV float rot1(float v)
-{
-    const int i = __builtin_bit_cast(int, v);
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(i, 0x09, 0xf, 0xf, true));   // 1, 2, 0, 0
-}
-PK_DEV float rot2(float v)
-{
-    const int i = __builtin_bit_cast(int, v);
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(i, 0x52, 0xf, 0xf, true));   // 2, 0, 1, 1
-}
-
 PK_DEV float quad_max(float v)
 {
     const int a = __builtin_bit_cast(int, v);
