@@ -63,7 +63,9 @@ typedef struct pk_ctx pk_ctx;
 
 /* Kernel variants for pk_lm_options.variant. */
 #define PK_VARIANT_AUTO 0     /* pick by robot shape and the autotune table  */
-#define PK_VARIANT_LANE 1     /* one problem per lane; star-of-chains robots  */
+#define PK_VARIANT_LANE 1     /* one lane per problem, or four where that leaves
+                                 SIMDs idle (same results): single chains and the
+                                 star of chains                               */
 #define PK_VARIANT_WAVE 2     /* one problem per 64-lane wavefront; any tree:
                                  the path-pair layout where it applies, else
                                  the lane-per-joint layout                    */
@@ -198,14 +200,15 @@ typedef struct {
 /* Context on one device (ordinal as seen by HIP).  Allocates the context's
  * device-side tables. */
 int pk_create(pk_ctx **out, int device_ordinal);
+/* Waits for the device, so that no call of ctx is in flight, then frees. */
 int pk_destroy(pk_ctx *ctx);
 /* Message of the last failed call on ctx (never NULL; ctx may be NULL). */
 const char *pk_last_error(pk_ctx *ctx);
 
 /* Copies the tree to the device (FP32) and returns its id.  Validates shape,
  * parent order, unit axes (within 1e-3; renormalised), limits, joint kinds
- * and EE references; folds fixed joints.  The per-lane kernel
- * (PK_VARIANT_LANE) serves single chains of 2 to 10 joints (revolute or
+ * and EE references; folds fixed joints.  The lane kernels
+ * (PK_VARIANT_LANE) serve single chains of 2 to 10 joints (revolute or
  * prismatic) ending in one EE and the star of 4 chains x 4 revolute joints
  * with 4 position EEs; other robots, and robots with mimic joints, run on
  * the per-wavefront kernel (PK_VARIANT_LANE is unsupported for them).  The
@@ -298,8 +301,8 @@ typedef struct {
                                     PK_SCHED_PER_GROUP: each
                                     group's persistent launches on a stream of its
                                     own, the groups running concurrently         */
-    int32_t variant[PK_MAX_GROUPS];  /* per group: lanes per problem, PK_VARIANT_LANE (1)
-                                        or PK_VARIANT_WAVE (64); PK_VARIANT_AUTO = the
+    int32_t variant[PK_MAX_GROUPS];  /* per group: lanes per problem, PK_VARIANT_LANE (1
+                                        or 4) or PK_VARIANT_WAVE (64); PK_VARIANT_AUTO = the
                                         options' choice                          */
 } pk_sched_options;              /* k and waves_per_cu zero = the autotuned entry if any */
 

@@ -218,10 +218,12 @@ hipError_t launch_groups(const MixedArgs &a, int &g0, int32_t *item_end, int32_t
 // Whether one launch serves the whole round: the batch has more than one kernel
 // and the kernel with every path holds all its trees at once (they are first in
 // the queue).  Then they run beside the other items; split, the launches' times
-// add up.  Past that they queue behind each other there.  60000 arms and 20000
-// hands with 400, 1000 and 2000 trees, 50 iterations, in us: 523, 607 and 810 in
-// one launch; with a line that split them (hands still one per lane): 1121, 1171
-// and 1260.
+// add up.  Past that they queue behind each other there.  50 iterations, 8
+// wavefronts per CU (so up to 2048 trees), one launch against split, us: 60000
+// arms and 20000 hands with 200 trees 498 / 728, 1000 585 / 774, 2048 812 / 854,
+// 2300 1026 / 924, 4096 1347 / 1123; 1000 arms and 1000 hands with 2048 652 / 761,
+// 2300 1015 / 832; 100000 arms and 2000 hands with 2048 877 / 849.  With 4 per CU (up
+// to 1024): 60000 and 20000 with 500 559 / 775, 1000 822 / 799, 1500 1048 / 854.
 bool one_launch(const MixedArgs &a, int wpc, int cus, int wg)
 {
     int64_t trees = 0;

@@ -22,12 +22,12 @@
 // bit for bit.  Control flow is uniform over a quad: a lane that reads
 // another by quad_perm finds it active.
 //
-// Bound: one wavefront's instruction stream (about 1.2 k instructions per
-// iteration for 7 joints, and the latencies that one wavefront per SIMD does
-// not hide).  Against one lane per problem, 30 iterations: 8 problems of 7
-// joints 135 -> 84 us; 16384 of the mobile base (10 joints) 192 -> 112; 16384 of
-// 7 joints without the rest term, where most steps end in the FP64 re-solve,
-// 180 -> 97.
+// Bound: one wavefront's instruction stream: about 1.2 k instructions per pass
+// for 7 joints, 1.07 k of them VALU, so 55 of a launch's 85 us; the rest is
+// latencies that one wavefront per SIMD does not hide.  Against one lane per
+// problem, 30 iterations: 8 problems of 7 joints 144 -> 85 us; 16384 of the
+// mobile base (10 joints) 192 -> 112; 16384 of 7 joints without the rest term,
+// where most steps end in the FP64 re-solve, 236 -> 104.
 #pragma once
 
 #include "lm_lane_kernels.hpp"

@@ -159,10 +159,8 @@ struct BestOut {
 // Launchers (defined next to their kernels).  Return hipSuccess or the
 // launch error.
 bool lane_variant_available(int chains, int chain_len, int kind);
-// Whether a plain launch (no queue, no active list) can take best-of-K
-// itself: K divides 64, so that a target's problems share a wavefront, or the
-// batch runs with four lanes per problem and K is at most 64, so that they
-// share a workgroup.  Reads P.K, P.N and P.target_exit.
+// Whether a plain launch (no queue, no active list) can take best-of-K itself
+// (lane::takes_best).  Reads P.K, P.N, the options and the weights.
 bool lane_takes_best(const RobotC &host_robot, const SolveParams &P);
 // persist_blocks: grid size when P.queue_head is set (0 = one block per item).
 // best (where lane_takes_best): best-of-K in the same launch.

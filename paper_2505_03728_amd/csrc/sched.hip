@@ -3,10 +3,11 @@
 //
 //  * A round runs every unfinished problem of every group for at most k more
 //    LM iterations.  A plan kernel turns the groups' active-list sizes into
-//    work items (a wavefront's problems on the group's device path), the wavefronts of one persistent launch per kernel pop items from
-//    its device queue and branch to the item's device path (lm_mixed.hip), and
-//    a compaction kernel packs the problems still unfinished into the next
-//    round's active lists, so problems that exited early stop taking lanes.
+//    work items (a wavefront's problems on the group's device path), the
+//    wavefronts of one persistent launch per kernel pop items from its device
+//    queue and branch to the item's device path (lm_mixed.hip), and a compaction
+//    kernel packs the problems still unfinished into the next round's active
+//    lists, so problems that exited early stop taking lanes.
 //  * Problem state stays in HBM between rounds (resumable kernels).
 //  * The chain of rounds plus the per-group best-of-K is captured once into a
 //    hipGraph per (buffers, options, schedule) and replayed.

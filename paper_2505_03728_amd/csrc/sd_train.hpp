@@ -97,7 +97,8 @@ PK_DEV void row_prefetch(bf16x8 (&b)[RING][NT], const __bf16 *__restrict__ wb)
 
 // The row pass: 32 rows per workgroup, all layers.  The activation tile
 // (later the gradient tile) and the last hidden layer's pre-activations stay
-// in LDS, the other pre-activations in registers; weights stream from L2 in
+// in LDS, the other pre-activations in registers (with 128 of them 19 values of
+// the widest and deepest net go through scratch memory); weights stream from L2 in
 // fragment order, a layer's first steps fetched before the previous layer's
 // epilogue.
 //

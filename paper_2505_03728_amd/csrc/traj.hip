@@ -458,7 +458,8 @@ PK_DEV void scale_columns(double *band, const double *invd, int V, int c0, int t
 // With two barriers per block, the next block's columns updated through LDS
 // by the whole workgroup and two register slots per lane in the backward
 // solve, 1024 trajectories of 32 x 7 variables took 3.10 ms and 37 of 25 x 6
-// (one workgroup's time) 0.979 ms; now 2.74 and 0.809.
+// (one workgroup's time) 0.979 ms; now 2.74 and 0.805.  (7 joints: 20 of the 256
+// registers' values are spilled, reloaded once per iteration.)
 template <int NJ>
 PK_DEV bool band_solve(TrajLds<NJ> &S, int V, float thresh_rel, const int (&mpb)[Pairs<NJ>::PB], int tid)
 {
