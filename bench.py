@@ -40,7 +40,7 @@ BF16_MFMA_PEAK = 2500.0     # TFLOP/s, MI355X dense BF16 matrix cores (datasheet
 LANE_KERNEL_SOURCES = ["paper_2505_03728_amd/csrc/lm_lane.hip", "paper_2505_03728_amd/csrc/lm_lane.hpp",
                        "paper_2505_03728_amd/csrc/lm_lane_kernels.hpp", "paper_2505_03728_amd/csrc/pk_device.hpp",
                        "paper_2505_03728_amd/csrc/pk_internal.hpp", "include/pkmi.h"]
-ARM_TRAFFIC = {"sha256": "65c23e297890bb2e", "fetch_kib": 2840.0, "write_kib": 7680.0, "fetch_scale": 2.0,
+ARM_TRAFFIC = {"sha256": "c1eff85295871077", "fetch_kib": 2838.0, "write_kib": 7680.0, "fetch_scale": 2.0,
                "write_scale": 1.0,
                "workload": {"targets": 16384, "K": 8, "max_iters": 30, "early_exit": True},
                "profile": "profiles/lm_lane_arm131k_hbm_counters.md"}
@@ -654,7 +654,8 @@ def run_mixed(args):
                              "(4 fingertip positions) + 4096 34-DoF tree problems, early exit, <= 50 "
                              "iterations", "problems": N, "schedule": mode, "iters_per_launch": k,
                  "waves_per_cu": wpc, "workgroup_size": wg,
-                 "lanes_per_problem": {g["tree"].name: (1 if v == pk.VARIANT_LANE else 64)
+                 "lanes_per_problem": {g["tree"].name: (64 if v != pk.VARIANT_LANE else
+                                                         4 if ctx.robot_info(g["rid"])["chains"] == 4 else 1)
                                        for g, v in zip(groups, variants)}},
                 success_rate=conv / N, groups=per, ms_separate_launches=round(ms_sep, 5),
                 ms_other_schedule={"schedule": "per-group launches" if other == pk.SCHED_PER_GROUP
