@@ -12,12 +12,12 @@ constexpr int THREADS = 4 * PROBLEMS;
 // kernel.
 __global__ __launch_bounds__(THREADS) void lm_star_kernel(const RobotC *__restrict__ rb,
                                                           const float *__restrict__ qr, SolveParams P, BestOut B,
-                                                          int per_block)
+                                                          int per_block, int64_t block0)
 {
     __shared__ float bc[PROBLEMS], bp[PROBLEMS];
     __shared__ int bv[PROBLEMS];
     const int slot = threadIdx.x >> 2, c = threadIdx.x & 3;
-    const int64_t p = (int64_t)blockIdx.x * per_block + slot;   // (place in the active list, if there is one)
+    const int64_t p = (block0 + blockIdx.x) * per_block + slot;   // (place in the active list, if there is one)
     const bool live = slot < per_block && p < (P.n_active ? (int64_t)*P.n_active : P.N);
     Final fin;
     if (live) star_problem<false>(rb, qr, P, p, &fin);
@@ -75,9 +75,11 @@ hipError_t launch(const RobotC *rb, const SolveParams &P, int persist_blocks, hi
     }
     const BestOut B = best ? *best : BestOut{nullptr, nullptr, nullptr};
     const int per_block = lane::quad_per_block(P.K, best != nullptr);
-    const dim3 grid((unsigned)((P.N + per_block - 1) / per_block));
-    hipLaunchKernelGGL(lm_star_kernel, grid, dim3(THREADS), 0, s, rb, qr, P, B, per_block);
-    return hipGetLastError();
+    // (four threads a problem: above 2^30 problems one launch cannot hold them)
+    return launch_parts((P.N + per_block - 1) / per_block, THREADS, [&](int64_t block0, unsigned blocks) {
+        hipLaunchKernelGGL(lm_star_kernel, dim3(blocks), dim3(THREADS), 0, s, rb, qr, P, B, per_block, block0);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace star

@@ -156,6 +156,21 @@ struct BestOut {
     int32_t *success;
 };
 
+// A grid has fewer than 2^32 threads (HIP takes the number modulo that, without
+// an error).  launch_parts calls launch(first workgroup, workgroups) for parts of
+// a grid of any size; it stops at the first error.
+inline int64_t max_blocks(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
+
+template <class Launch>
+hipError_t launch_parts(int64_t blocks, int threads, Launch launch)
+{
+    const int64_t most = max_blocks(threads);
+    hipError_t e = hipSuccess;
+    for (int64_t b = 0; b < blocks && e == hipSuccess; b += most)
+        e = launch(b, (unsigned)(blocks - b < most ? blocks - b : most));
+    return e;
+}
+
 // Launchers (defined next to their kernels).  Return hipSuccess or the
 // launch error.
 bool lane_variant_available(int chains, int chain_len, int kind);

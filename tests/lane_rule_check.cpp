@@ -1,7 +1,8 @@
 // CPU check of the rule that sends a batch to the kernel with four lanes per
 // problem (lane_rule.hpp): over batch sizes, seeds per target and chain lengths
 // the workgroups of the launch it chooses stay at two per CU of 256 (one from 9
-// joints), counted as the kernel counts them.  Prints one line per failure.
+// joints), counted as the kernel counts them; and the parts that a batch too large
+// for one launch is split into.  Prints one line per failure.
 #include <cstdio>
 #include <cstring>
 
@@ -62,6 +63,24 @@ int main()
     line("8 joints, FP64 steps", 8, PK_EE_POSE, 0.f, 1, false, 32768);
     line("8 joints, position", 8, PK_EE_POSITION, 0.01f, 1, false, 32768);
     line("9 joints", 9, PK_EE_POSE, 0.f, 1, false, 16384);
+    // parts of a launch: every workgroup once, each part under 2^32 threads
+    const int64_t big = (int64_t)1 << 31;
+    for (int64_t n : {(int64_t)1, (int64_t)64, (int64_t)65, big / 2, big / 2 + 1, big - 1, 4 * big + 3})
+        for (int per_block : {1, 33, 64})
+            for (int threads : {64, 256}) {
+                const int64_t all = (n + per_block - 1) / per_block;
+                int64_t next = 0;
+                bool ok = true;
+                const hipError_t e = launch_parts(all, threads, [&](int64_t b, unsigned blocks) {
+                    ok = ok && b == next && blocks > 0 && (int64_t)blocks * threads < ((int64_t)1 << 32);
+                    next = b + blocks;
+                    return hipSuccess;
+                });
+                if (!ok || e != hipSuccess || next != all) {
+                    ++failures;
+                    printf("FAIL parts of %lld workgroups of %d threads\n", (long long)all, threads);
+                }
+            }
     SolveParams P = batch(10, 2, 0.f);
     P.target_exit = 1;
     if (lane::takes_quad(1, 7, PK_EE_POSE, P, false) || lane::takes_star(4, 4, P)) {
