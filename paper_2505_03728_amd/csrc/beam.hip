@@ -66,10 +66,10 @@ PK_DEV uint64_t beam_load(const int32_t *status, const float *cost, const float 
 __global__ __launch_bounds__(64 * BEAM_TARGETS_PER_BLOCK) void beam_rank_kernel(
     int64_t T, int K, int keep, int n, const int32_t *__restrict__ status, const float *__restrict__ cost,
     const float *__restrict__ pcost, const float *__restrict__ joints, int32_t *__restrict__ kept,
-    float *__restrict__ seeds1)
+    float *__restrict__ seeds1, int64_t block0)
 {
     const int k = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * BEAM_TARGETS_PER_BLOCK + (threadIdx.x >> 6);
+    const int64_t t = (block0 + blockIdx.x) * BEAM_TARGETS_PER_BLOCK + (threadIdx.x >> 6);
     if (t >= T) return;   // (the whole wavefront)
     bool conv;
     float c;
@@ -97,10 +97,10 @@ struct PickArgs {
 // Per target (a wavefront): the first of its `keep` stage-1 results in the
 // survivor order; its values copied by a lane each.  1000 targets, 4 kept:
 // 6.5 us with a thread per target, 4.5 now.
-__global__ __launch_bounds__(64 * BEAM_TARGETS_PER_BLOCK) void beam_pick_kernel(PickArgs a)
+__global__ __launch_bounds__(64 * BEAM_TARGETS_PER_BLOCK) void beam_pick_kernel(PickArgs a, int64_t block0)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * BEAM_TARGETS_PER_BLOCK + (threadIdx.x >> 6);
+    const int64_t t = (block0 + blockIdx.x) * BEAM_TARGETS_PER_BLOCK + (threadIdx.x >> 6);
     if (t >= a.T) return;   // (the whole wavefront)
     const int64_t N1 = a.T * a.keep, base = t * a.keep;
     bool conv;
@@ -119,8 +119,6 @@ __global__ __launch_bounds__(64 * BEAM_TARGETS_PER_BLOCK) void beam_pick_kernel(
         if (a.best_rot) a.best_rot[(int64_t)e * a.T + t] = a.rot_err[(int64_t)e * N1 + p];
     }
 }
-
-inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 }  // namespace pk
@@ -209,11 +207,14 @@ extern "C" int pk_ik_beam(pk_ctx *ctx, int32_t robot_id, int64_t T, const float 
     P0.joints = joints0; P0.cost = cost0; P0.pose_cost = pcost0; P0.status = status0;
     PK_HIP(ctx, launch_lm(*rb, P0, v0, s));
     // Survivors -> stage-1 seeds.
-    hipLaunchKernelGGL(beam_rank_kernel, dim3(nblk(T, BEAM_TARGETS_PER_BLOCK)),
-                       dim3(64 * BEAM_TARGETS_PER_BLOCK), 0, s, T, K, keep, n,
-                       (const int32_t *)status0, (const float *)cost0, (const float *)pcost0,
-                       (const float *)joints0, kept, seeds1);
-    PK_HIP(ctx, hipGetLastError());
+    const int64_t select_blocks = (T + BEAM_TARGETS_PER_BLOCK - 1) / BEAM_TARGETS_PER_BLOCK;
+    constexpr int SELECT_THREADS = 64 * BEAM_TARGETS_PER_BLOCK;
+    PK_HIP(ctx, launch_parts(select_blocks, SELECT_THREADS, [&](int64_t block0, unsigned blocks) {
+        hipLaunchKernelGGL(beam_rank_kernel, dim3(blocks), dim3(SELECT_THREADS), 0, s, T, K, keep, n,
+                           (const int32_t *)status0, (const float *)cost0, (const float *)pcost0,
+                           (const float *)joints0, kept, seeds1, block0);
+        return hipGetLastError();
+    }));
     // Stage 1: the survivors, LM started afresh.
     P1.K = keep; P1.N = N1; P1.T = T;
     P1.targets = targets; P1.seeds = seeds1;
@@ -226,8 +227,9 @@ extern "C" int pk_ik_beam(pk_ctx *ctx, int32_t robot_id, int64_t T, const float 
     a.pos_err = pos1; a.rot_err = rot1;
     a.best_joints = out->best_joints; a.best_pos = out->pos_err; a.best_rot = out->rot_err;
     a.best_cost = out->cost; a.best_index = out->best_index; a.success = out->target_success;
-    hipLaunchKernelGGL(beam_pick_kernel, dim3(nblk(T, BEAM_TARGETS_PER_BLOCK)),
-                       dim3(64 * BEAM_TARGETS_PER_BLOCK), 0, s, a);
-    PK_HIP(ctx, hipGetLastError());
+    PK_HIP(ctx, launch_parts(select_blocks, SELECT_THREADS, [&](int64_t block0, unsigned blocks) {
+        hipLaunchKernelGGL(beam_pick_kernel, dim3(blocks), dim3(SELECT_THREADS), 0, s, a, block0);
+        return hipGetLastError();
+    }));
     return PK_OK;
 }

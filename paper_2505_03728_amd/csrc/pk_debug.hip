@@ -49,11 +49,11 @@ constexpr int FK_BLOCK = 64;
 
 template <bool FRAMES>
 __global__ __launch_bounds__(FK_BLOCK) void fk_kernel(const RobotC *__restrict__ rb, int64_t N,
-                                                      const float *__restrict__ q,
-                                                      float *ee_pose, float *joint_frames)
+                                                      const float *__restrict__ q, float *ee_pose,
+                                                      float *joint_frames, int64_t block0)
 {
     extern __shared__ float saved[];   // [slot][12][FK_BLOCK]
-    const int64_t p = (int64_t)blockIdx.x * FK_BLOCK + threadIdx.x;
+    const int64_t p = (block0 + blockIdx.x) * FK_BLOCK + threadIdx.x;
     if (p >= N) return;   // each lane reads only what it wrote itself: no barrier
     float *mine = saved + threadIdx.x;
     const int n = rb->n;
@@ -122,9 +122,9 @@ __global__ __launch_bounds__(FK_BLOCK) void fk_kernel(const RobotC *__restrict__
 __global__ __launch_bounds__(64) void resjac_kernel(const RobotC *__restrict__ rb, int64_t N,
                                                     int32_t K, const float *__restrict__ targets,
                                                     const float *__restrict__ q, SolveParams P,
-                                                    float *r, float *J)
+                                                    float *r, float *J, int64_t block0)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t p = (block0 + blockIdx.x) * blockDim.x + threadIdx.x;
     if (p >= N) return;
     const int64_t T = N / K, t = p / K;
     float O[PK_MAX_JOINTS][9], pos[PK_MAX_JOINTS][3];
@@ -231,12 +231,14 @@ hipError_t launch_fk(const RobotC *rb, const RobotC &host, int64_t N, const floa
 {
     // at most PK_FK_MAX_SLOTS slots of 3 KB
     const size_t lds = (size_t)host.fk_slots * 12 * FK_BLOCK * sizeof(float);
-    const dim3 grid((unsigned)((N + FK_BLOCK - 1) / FK_BLOCK)), block(FK_BLOCK);
-    if (joint_frames)
-        hipLaunchKernelGGL(fk_kernel<true>, grid, block, lds, s, rb, N, q, ee_pose, joint_frames);
-    else
-        hipLaunchKernelGGL(fk_kernel<false>, grid, block, lds, s, rb, N, q, ee_pose, joint_frames);
-    return hipGetLastError();
+    return launch_parts((N + FK_BLOCK - 1) / FK_BLOCK, FK_BLOCK, [&](int64_t block0, unsigned blocks) {
+        const dim3 grid(blocks), block(FK_BLOCK);
+        if (joint_frames)
+            hipLaunchKernelGGL(fk_kernel<true>, grid, block, lds, s, rb, N, q, ee_pose, joint_frames, block0);
+        else
+            hipLaunchKernelGGL(fk_kernel<false>, grid, block, lds, s, rb, N, q, ee_pose, joint_frames, block0);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_residual_jacobian(const RobotC *rb, int64_t N, int32_t K, const float *targets,
@@ -244,9 +246,10 @@ hipError_t launch_residual_jacobian(const RobotC *rb, int64_t N, int32_t K, cons
                                     hipStream_t s)
 {
     const int block = 64;
-    hipLaunchKernelGGL(resjac_kernel, dim3((unsigned)((N + block - 1) / block)), dim3(block), 0, s,
-                       rb, N, K, targets, q, P, r, J);
-    return hipGetLastError();
+    return launch_parts((N + block - 1) / block, block, [&](int64_t block0, unsigned blocks) {
+        hipLaunchKernelGGL(resjac_kernel, dim3(blocks), dim3(block), 0, s, rb, N, K, targets, q, P, r, J, block0);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_best_of_k(const SolveParams &P, int n, int32_t *best_index, float *best_joints,

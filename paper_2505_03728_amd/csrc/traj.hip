@@ -747,15 +747,25 @@ inline bool traj_variant(int n) { return n == 4 || n == 6 || n == 7 || n == 10; 
 
 hipError_t launch_traj(const RobotC *rb, int n, const TrajParams &P, hipStream_t s)
 {
-    const dim3 grid((unsigned)P.B), block(TRAJ_THREADS);
-    switch (n) {
-    case 4: hipLaunchKernelGGL(traj_kernel<4>, grid, block, 0, s, rb, P); break;
-    case 6: hipLaunchKernelGGL(traj_kernel<6>, grid, block, 0, s, rb, P); break;
-    case 7: hipLaunchKernelGGL(traj_kernel<7>, grid, block, 0, s, rb, P); break;
-    case 10: hipLaunchKernelGGL(traj_kernel<10>, grid, block, 0, s, rb, P); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return launch_parts(P.B, TRAJ_THREADS, [&](int64_t b, unsigned blocks) {
+        // trajectory b is the part's first (planes keep their stride P.B)
+        TrajParams Q = P;
+        Q.start += b; Q.goal += b;
+        Q.init += b * P.T * n; Q.out += b * P.T * n;
+        for (float **p : {&Q.cost, &Q.pos_err, &Q.rot_err})
+            if (*p) *p += b;
+        for (int32_t **p : {&Q.iters, &Q.accepts, &Q.status})
+            if (*p) *p += b;
+        const dim3 grid(blocks), block(TRAJ_THREADS);
+        switch (n) {
+        case 4: hipLaunchKernelGGL(traj_kernel<4>, grid, block, 0, s, rb, Q); break;
+        case 6: hipLaunchKernelGGL(traj_kernel<6>, grid, block, 0, s, rb, Q); break;
+        case 7: hipLaunchKernelGGL(traj_kernel<7>, grid, block, 0, s, rb, Q); break;
+        case 10: hipLaunchKernelGGL(traj_kernel<10>, grid, block, 0, s, rb, Q); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    });
 }
 
 }  // namespace
