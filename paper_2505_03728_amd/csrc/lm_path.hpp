@@ -753,7 +753,7 @@ PK_DEV void path_problem(const RobotC *__restrict__ rb, KParams *Pk, float *lds,
     }
 }
 
-struct PathKernelArgs {     // the first arguments of lm_path_kernel, for the offset of P
+struct PathKernelArgs {     // the argument list of lm_path_kernel, for the offset of P
     const RobotC *rb;
     SolveParams P;
 };
@@ -764,13 +764,13 @@ struct PathKernelArgs {     // the first arguments of lm_path_kernel, for the of
 // the per-problem set-up and in the FP64 re-solve, not in the LM loop).
 template <int DMAX, int MMAX, int RW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MMAX <= 4 ? 4 : 3))) void lm_path_kernel(
-    const RobotC *__restrict__ rb, SolveParams P, int64_t block0)
+    const RobotC *__restrict__ rb, SolveParams P)
 {
     KParams *Pk = kernel_params_at(offsetof(PathKernelArgs, P));
     using L = Lds<DMAX, MMAX>;
     __shared__ __attribute__((aligned(16))) float lds[L::FLOATS];
     const int64_t nact = P.n_active ? (int64_t)*P.n_active : P.N;
-    int64_t wi = P.queue_head ? wave::pop_item_wave(P.queue_head) : block0 + blockIdx.x;
+    int64_t wi = P.queue_head ? wave::pop_item_wave(P.queue_head) : (int64_t)blockIdx.x;
     while (wi < nact) {
         path_problem<DMAX, MMAX, RW>(rb, Pk, lds, wi);
         if (!P.queue_head) break;
@@ -782,10 +782,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MMAX <= 4 ? 
 template <int DMAX, int MMAX, int RW>
 hipError_t launch_path(const RobotC *rb, const SolveParams &P, int persist_blocks, hipStream_t s)
 {
-    int64_t grid = P.N;
-    if (P.queue_head) grid = std::min({grid, persist_blocks > 0 ? (int64_t)persist_blocks : grid, max_blocks(64)});
-    return launch_parts(grid, 64, [&](int64_t block0, unsigned blocks) {
-        hipLaunchKernelGGL((lm_path_kernel<DMAX, MMAX, RW>), dim3(blocks), dim3(64), 0, s, rb, P, block0);
+    return wavefront_launches(P, persist_blocks, [&](const SolveParams &Q, unsigned blocks) {
+        hipLaunchKernelGGL((lm_path_kernel<DMAX, MMAX, RW>), dim3(blocks), dim3(64), 0, s, rb, Q);
         return hipGetLastError();
     });
 }

@@ -25,8 +25,6 @@
 
 #include <math.h>
 
-#include <algorithm>
-
 #include "pk_device.hpp"
 
 namespace pk {
@@ -697,12 +695,12 @@ PK_DEV int64_t pop_item_wave(int32_t *head)
 }
 
 template <int DMAX, int MMAX>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((DMAX <= 16 && MMAX <= 4) ? 2 : 1))) void lm_wave_kernel(const RobotC *__restrict__ rb, SolveParams P, int64_t block0)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((DMAX <= 16 && MMAX <= 4) ? 2 : 1))) void lm_wave_kernel(const RobotC *__restrict__ rb, SolveParams P)
 {
     using L = Lds<DMAX, MMAX>;
     __shared__ __attribute__((aligned(16))) float lds[L::FLOATS];
     const int64_t nact = P.n_active ? (int64_t)*P.n_active : P.N;
-    int64_t wi = P.queue_head ? pop_item_wave(P.queue_head) : block0 + blockIdx.x;
+    int64_t wi = P.queue_head ? pop_item_wave(P.queue_head) : (int64_t)blockIdx.x;
     while (wi < nact) {
         wave_problem<DMAX, MMAX>(rb, P, lds, wi);
         if (!P.queue_head) break;
@@ -714,10 +712,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((DMAX <= 16 
 template <int DMAX, int MMAX>
 hipError_t launch_wave(const RobotC *rb, const SolveParams &P, int persist_blocks, hipStream_t s)
 {
-    int64_t grid = P.N;
-    if (P.queue_head) grid = std::min({grid, persist_blocks > 0 ? (int64_t)persist_blocks : grid, max_blocks(64)});
-    return launch_parts(grid, 64, [&](int64_t block0, unsigned blocks) {
-        hipLaunchKernelGGL((lm_wave_kernel<DMAX, MMAX>), dim3(blocks), dim3(64), 0, s, rb, P, block0);
+    return wavefront_launches(P, persist_blocks, [&](const SolveParams &Q, unsigned blocks) {
+        hipLaunchKernelGGL((lm_wave_kernel<DMAX, MMAX>), dim3(blocks), dim3(64), 0, s, rb, Q);
         return hipGetLastError();
     });
 }

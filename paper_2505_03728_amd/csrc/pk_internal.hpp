@@ -171,6 +171,49 @@ hipError_t launch_parts(int64_t blocks, int threads, Launch launch)
     return e;
 }
 
+// The problems of a plain batch (no active list) from p0 on, p0 a multiple of K or
+// inside the last target the part has problems of: the same planes and strides
+// (N, T), read and written from p0.
+inline SolveParams batch_from(const SolveParams &P, int64_t p0)
+{
+    SolveParams Q = P;
+    Q.targets += p0 / P.K;
+    Q.seeds += p0;
+    for (float **p : {&Q.joints, &Q.pos_err, &Q.rot_err, &Q.pose_cost, &Q.cost, &Q.trace_q})
+        if (*p) *p += p0;
+    for (int32_t **p : {&Q.iters, &Q.accepts, &Q.status, &Q.iters_to_tol, &Q.trace_acc})
+        if (*p) *p += p0;
+    return Q;
+}
+
+// Problems of the part of a batch that starts at p0: at most `most`, whole
+// targets of K where one fits, else no more than the rest of p0's target (so that
+// its problems' targets count from 0).
+inline int64_t part_size(int64_t N, int64_t K, int64_t p0, int64_t most)
+{
+    const int64_t n = K <= most ? most / K * K : K - p0 % K < most ? K - p0 % K : most;
+    return n < N - p0 ? n : N - p0;
+}
+
+// Launches of a kernel with a wavefront per problem: launch(batch, workgroups)
+// with a queue once, else for each part that fits a grid.
+template <class Launch>
+hipError_t wavefront_launches(const SolveParams &P, int persist_blocks, Launch launch)
+{
+    const int64_t most = max_blocks(64);
+    if (P.queue_head || P.N <= most) {
+        int64_t grid = P.N < most ? P.N : most;
+        if (P.queue_head && persist_blocks > 0 && persist_blocks < grid) grid = persist_blocks;
+        return launch(P, (unsigned)grid);
+    }
+    hipError_t e = hipSuccess;
+    for (int64_t p0 = 0, n; p0 < P.N && e == hipSuccess; p0 += n) {
+        n = part_size(P.N, P.K, p0, most);
+        e = launch(batch_from(P, p0), (unsigned)n);
+    }
+    return e;
+}
+
 // Launchers (defined next to their kernels).  Return hipSuccess or the
 // launch error.
 bool lane_variant_available(int chains, int chain_len, int kind);

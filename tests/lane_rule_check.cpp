@@ -81,6 +81,23 @@ int main()
                     printf("FAIL parts of %lld workgroups of %d threads\n", (long long)all, threads);
                 }
             }
+    // parts of a batch with a wavefront per problem: a problem's target in its part
+    // is its target in the batch
+    for (int64_t K : {(int64_t)1, (int64_t)3, (int64_t)64, (int64_t)99, (int64_t)100, (int64_t)101, (int64_t)250, (int64_t)1000})
+        for (int64_t N = K; N <= 2000; N += K) {
+            int64_t p0 = 0, n;
+            for (; p0 < N; p0 += n) {
+                n = part_size(N, K, p0, 100);
+                bool ok = n > 0 && n <= 100;
+                for (int64_t p = 0; ok && p < n; ++p) ok = p0 / K + p / K == (p0 + p) / K;
+                if (!ok) {
+                    ++failures;
+                    printf("FAIL part at %lld of %lld, K=%lld: %lld\n", (long long)p0, (long long)N, (long long)K, (long long)n);
+                    break;
+                }
+            }
+            if (p0 != N) ++failures;
+        }
     SolveParams P = batch(10, 2, 0.f);
     P.target_exit = 1;
     if (lane::takes_quad(1, 7, PK_EE_POSE, P, false) || lane::takes_star(4, 4, P)) {
